@@ -76,8 +76,10 @@ typedef enum { NYSTRA_LM_POOL2D = 0, NYSTRA_LM_SEGMENT1D = 1 } nystra_landmark_m
 /* Kernel family.  AUTO picks, for nystra_attn_forward_ex, the MFMA-tiled
  * kernel when the shape is one it covers and the pointers are aligned as it
  * needs (for bf16, Q, K, V and O to 4 bytes; fp32 needs nothing beyond the
- * element size), and the generic kernel otherwise; nystra_attn_forward_ws may in addition pick the
- * token-split kernels (see there).  The other values force one
+ * element size), and the generic family otherwise (which AUTO runs on a tiled
+ * kernel with a partial last tile where only N % 16 != 0 stands against it);
+ * nystra_attn_forward_ws may in addition pick the token-split kernels (see
+ * there).  The other values force one
  * (NYSTRA_ERR_UNSUPPORTED if it cannot run this shape, or -- for SPLIT -- if
  * the entry point takes no workspace). */
 typedef enum {

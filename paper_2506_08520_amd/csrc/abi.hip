@@ -126,6 +126,13 @@ bool split_preferred(const Problem &p)
     return p.N >= 4096 || (p.N >= 2048 && p.units < 512);
 }
 
+// What AUTO runs on a shape that only the generic family accepts by name (N not
+// a multiple of 16) but the tiled kernels cover with a partial last tile: 10 x 10
+// windows, m = 25, d_h = 16, 3072 units fp32 took 1270 us in the generic kernel
+// and 86 us tiled.  nystra_select_variant() reports it as GENERIC, and
+// forcing TILED on such a shape stays refused.
+constexpr int kVariantRagged = 100;
+
 // Resolves options and the problem; does not touch device memory.  with_ws
 // says whether the entry point takes a workspace (and so may run the
 // token-split kernels).
@@ -177,9 +184,20 @@ int build_problem(const void *Q, const void *K, const void *V, void *O, int n_wi
     default:
         *variant = (split && split_preferred(*p)) ? NYSTRA_VARIANT_SPLIT
                    : tiled                        ? NYSTRA_VARIANT_TILED
+                   : nystra::ragged_supported(*p) ? kVariantRagged
                                                   : NYSTRA_VARIANT_GENERIC;
         return NYSTRA_OK;
     }
+}
+
+// The families that take no scratch memory.
+hipError_t launch_one_pass(const Problem &p, int variant, hipStream_t s)
+{
+    if (variant == NYSTRA_VARIANT_TILED)
+        return nystra::launch_tiled_forward(p, s);
+    if (variant == kVariantRagged)
+        return nystra::launch_tiled_large(p, s);
+    return nystra::launch_generic_forward(p, s);
 }
 
 }  // namespace
@@ -215,9 +233,7 @@ int nystra_attn_forward_ex(const void *Q, const void *K, const void *V, void *O,
         return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     clear_stale_error();
-    if (variant == NYSTRA_VARIANT_TILED)
-        return finish_launch(nystra::launch_tiled_forward(p, s));
-    return finish_launch(nystra::launch_generic_forward(p, s));
+    return finish_launch(launch_one_pass(p, variant, s));
 }
 
 int nystra_attn_workspace_size(int n_windows, int heads, int N, int d_h, int m, int dtype,
@@ -266,9 +282,7 @@ int nystra_attn_forward_ws(const void *Q, const void *K, const void *V, void *O,
         return finish_launch(nystra::launch_split(p, workspace, s));
     }
     clear_stale_error();
-    if (variant == NYSTRA_VARIANT_TILED)
-        return finish_launch(nystra::launch_tiled_forward(p, s));
-    return finish_launch(nystra::launch_generic_forward(p, s));
+    return finish_launch(launch_one_pass(p, variant, s));
 }
 
 }  // extern "C"
@@ -328,11 +342,8 @@ int nystra_attn_forward_noalloc(const void *Q, const void *K, const void *V, voi
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     clear_stale_error();
-    if (variant != NYSTRA_VARIANT_SPLIT) {   // these kernels use no scratch memory
-        if (variant == NYSTRA_VARIANT_TILED)
-            return finish_launch(nystra::launch_tiled_forward(p, s));
-        return finish_launch(nystra::launch_generic_forward(p, s));
-    }
+    if (variant != NYSTRA_VARIANT_SPLIT)   // these kernels use no scratch memory
+        return finish_launch(launch_one_pass(p, variant, s));
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess)
@@ -462,7 +473,9 @@ int nystra_select_variant(int N, int d_h, int m, int dtype, const nystra_opts *o
     int variant = 0;
     int rc = build_problem(nullptr, nullptr, nullptr, nullptr, 1, 1, N, d_h, m, dtype, opts,
                            false, &p, &variant);
-    return rc == NYSTRA_OK ? variant : -rc;
+    if (rc != NYSTRA_OK)
+        return -rc;
+    return variant == kVariantRagged ? int(NYSTRA_VARIANT_GENERIC) : variant;
 }
 
 }  // extern "C"
@@ -631,10 +644,8 @@ int block_forward(const void *X, const void *Wqkv, const void *bqkv, const void 
         e = nystra::launch_exact(p, st);
     else if (bp.variant == NYSTRA_VARIANT_SPLIT)
         e = nystra::launch_split(p, attn_ws, st);
-    else if (bp.variant == NYSTRA_VARIANT_TILED && nystra::tiled_supported(p))
-        e = nystra::launch_tiled_forward(p, st);
     else
-        e = nystra::launch_generic_forward(p, st);
+        e = launch_one_pass(p, bp.variant, st);
     if (e != hipSuccess)
         return finish_launch(e);
     g.proj = true;

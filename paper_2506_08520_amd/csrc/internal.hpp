@@ -41,7 +41,9 @@ hipError_t launch_exact(const Problem &p, hipStream_t stream);
 // landmarks, the multi-wave kernel otherwise.
 bool tiled_supported(const Problem &p);
 hipError_t launch_tiled_forward(const Problem &p, hipStream_t stream);
+// ragged_supported(): the same kernels with a partial last token tile, any N.
 bool tiled_large_supported(const Problem &p);
+bool ragged_supported(const Problem &p);
 hipError_t launch_tiled_large(const Problem &p, hipStream_t stream);
 
 // Token-split kernels over a caller-provided workspace (global attention).

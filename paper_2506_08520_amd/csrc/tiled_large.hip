@@ -1,5 +1,6 @@
-// MFMA-tiled PnP-Nystra kernel for large windows (N a multiple of 16, e.g.
-// 16x16 and 32x32 windows; m <= 64 landmarks; d_h in {8, 12, ..., 28, 30, 32}).
+// MFMA-tiled PnP-Nystra kernel for large windows (16x16, 32x32, ...; N a
+// multiple of 16, and, in a variant with a partial last token tile, any N; m <= 64
+// landmarks; d_h in {8, 12, ..., 28, 30, 32}).
 //
 // One workgroup computes one (window, head) unit with MT = ceil(m / 16)
 // wavefronts; wave w owns landmark tile w (landmarks 16w .. 16w+15):
@@ -48,7 +49,12 @@ struct LargeArgs {
 // 2 = two tiles per image row (32 x 32 windows), any band height.  With KPL = 1 the registers
 // are held to 128 (four waves per SIMD, as without KP); the few values that
 // do not fit are saved once around the key pass, none inside it.
-template <class E, int MT, int D, bool BFM, bool FULL, int KPL>
+// RAG: any N.  The last token tile is partial (and, in pairs of tiles, the
+// last one may be missing): its absent rows repeat row N - 1 in the loads,
+// their logits become -inf and their V rows 0 after the products, and their O
+// rows are not stored.  The extra index arithmetic is paid only here, so
+// multiples of 16 keep the kernels without it.
+template <class E, int MT, int D, bool BFM, bool FULL, int KPL, bool RAG = false>
 __global__ void __launch_bounds__(64 * MT)
 __attribute__((amdgpu_waves_per_eu(KPL == 1 ? 4 : 1)))
 tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__restrict__ k,
@@ -69,7 +75,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
     const int lt = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int g = lane >> 4, c = lane & 15;
     float *vec = lds + L::vec + 64 * lt;
-    const int m = FULL ? 16 * MT : a.m, N = a.N, NT = a.N >> 4;
+    const int m = FULL ? 16 * MT : a.m, N = a.N, NT = RAG ? (a.N + 15) >> 4 : a.N >> 4;
     const int l = 16 * lt + c;            // this lane's landmark
     const bool lval = FULL || l < m;
     const int64_t base = int64_t(blockIdx.x) * N * d;
@@ -241,7 +247,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         for (int u = 0; u < 2; ++u) {
             // 32-bit offsets from the unit's (uniform) base: N d < 2^26
             const int tt = min(t0 + u, NT - 1);
-            const unsigned row = unsigned(16 * tt + c) * d;
+            const unsigned row = unsigned(RAG ? min(16 * tt + c, N - 1) : 16 * tt + c) * d;
             if constexpr (BFM)
                 kw_[u] = load_row8_bf16(ku16 + (row + chunk_start<D>(g)));
             else if constexpr (E::bytes == 4)
@@ -257,7 +263,27 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 const unsigned vrow = unsigned(16 * tt + 4 * g) * d + unsigned(min(f, d - 1));
                 const uint16_t *vp16 = vu16 + vrow;
                 const typename E::T *vp = vu + vrow;
-                if constexpr (BFM) {
+                if constexpr (RAG) {
+                    // rows past the end repeat row N - 1
+                    const unsigned f0 = unsigned(min(f, d - 1));
+                    unsigned at[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        at[x] = unsigned(min(16 * tt + 4 * g + x, N - 1)) * d + f0;
+                    if constexpr (BFM) {
+#pragma unroll
+                        for (int pp = 0; pp < 2; ++pp) {
+                            u16x2 pr;
+                            pr.x = vu16[at[2 * pp]];
+                            pr.y = vu16[at[2 * pp + 1]];
+                            vh_[u][ct][pp] = __builtin_bit_cast(uint32_t, pr);
+                        }
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < 4; ++x)
+                            vr_[u][ct][x] = E::load(vu, at[x]);
+                    }
+                } else if constexpr (BFM) {
 #pragma unroll
                     for (int pp = 0; pp < 2; ++pp) {
                         u16x2 pr;
@@ -295,6 +321,26 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 }
             }
         const bool second = t0 + 1 < NT;   // uniform
+        // RAG: keys of tile u from here on (4g + i >= vend[u]) are absent
+        const bool partial = RAG && 16 * (t0 + 2) > N;   // uniform
+        const int vend[2] = {N - 16 * t0, N - 16 * (t0 + 1)};
+        if (partial) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    if constexpr (BFM) {
+#pragma unroll
+                        for (int pp = 0; pp < 2; ++pp)
+                            vh_[u][ct][pp] &= (4 * g + 2 * pp < vend[u] ? 0xffffu : 0u) |
+                                              (4 * g + 2 * pp + 1 < vend[u] ? 0xffff0000u : 0u);
+                    } else {
+#pragma unroll
+                        for (int x = 0; x < 4; ++x)
+                            vr_[u][ct][x] = 4 * g + x < vend[u] ? vr_[u][ct][x] : 0.f;
+                    }
+                }
+        }
         bf8 vv[NCT];   // bf16 path: V of the pair as the right-hand operand
         if constexpr (BFM) {
 #pragma unroll
@@ -326,6 +372,13 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 // a repeated last tile (fp32 path, odd tile count) leaves the
                 // maximum unchanged, so it needs no exclusion here
                 gmax = fmaxf(gmax, fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3])));
+            }
+            if (partial) {   // repeated rows left the maximum as it is
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        su[u][i] = 4 * g + i < vend[u] ? su[u][i] : -INFINITY;
             }
             const float mnew = fmaxf(mrj[j], max_groups(gmax));
             // Rescale what is accumulated when a maximum grew; the factor is
@@ -576,7 +629,8 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
     auto load_q = [&](int t0, float (&qg_)[kQGroup][8], bf8 (&qw_)[kQGroup]) {
 #pragma unroll
         for (int u = 0; u < kQGroup; ++u) {
-            const int64_t row = int64_t(16 * min(t0 + u * MT, NT - 1) + c) * d;
+            const int tok = 16 * min(t0 + u * MT, NT - 1) + c;
+            const int64_t row = int64_t(RAG ? min(tok, N - 1) : tok) * d;
             if constexpr (BFM)
                 qw_[u] = load_row8_bf16(qu16 + row + chunk_start<D>(g));
             else if constexpr (E::bytes == 4)
@@ -625,12 +679,13 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                         od = fmaf(e, wdv[kk][i], od);
                 }
             f4 rcp;   // 1 / O_D[16tt + 4g + i]
+            f4 odv = {0.f, 0.f, 0.f, 0.f};
             if constexpr (!PAD) {
                 od = sum_groups(od);
-                const f4 odr = by_rows(od, vec, g, c);
+                odv = by_rows(od, vec, g, c);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    rcp[i] = __builtin_amdgcn_rcpf(odr[i]);
+                    rcp[i] = __builtin_amdgcn_rcpf(odv[i]);
             }
             bf8 gh[MP], gl[MP];
             if constexpr (BFM) {
@@ -669,11 +724,26 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 for (int i = 0; i < 4; ++i)
                     rcp[i] = __builtin_amdgcn_rcpf(row_bcast<D % 16>(ont[D / 16][i]));
             }
+            if constexpr (RAG && E::bytes == 4) {
+                // One Newton step (v_rcp_f32 is within 1 ulp, not rounded): the
+                // kernel this path replaces divided.  1 / 0 and 1 / inf stay.
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float od = PAD ? row_bcast<D % 16>(ont[D / 16 % 2][i]) : odv[i];
+                    const float e = fmaf(-od, rcp[i], 1.f);
+                    rcp[i] = fabsf(e) < 0.5f ? fmaf(e, rcp[i], rcp[i]) : rcp[i];
+                }
+            }
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct) {
                 const f4 on = ont[ct];
                 const int f = 16 * ct + c;
-                if (f < d) {
+                if (RAG && f < d && 16 * tt + 16 > N) {   // the partial tile
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (16 * tt + 4 * g + i < N)
+                            E::store(ou, int64_t(16 * tt + 4 * g + i) * d + f, on[i] * rcp[i]);
+                } else if (f < d) {
                     const int64_t orow = int64_t(16 * tt + 4 * g) * d + f;
                     if constexpr (E::bytes == 2) {
                         // rows (0, 1) and (2, 3) converted in pairs (round to
@@ -756,6 +826,16 @@ void launch_large_f(const Problem &p, const LargeArgs &a, hipStream_t stream)
 template <class E, int MT, int D>
 void launch_large(const Problem &p, const LargeArgs &a, hipStream_t stream)
 {
+    if (p.N % 16 != 0) {
+        const size_t lds = size_t(LargeLds<MT>::total) * sizeof(float);
+        hipLaunchKernelGGL((tiled_large_kernel<E, MT, D, E::bytes == 2, false, 0, true>),
+                           dim3(unsigned(p.units)), dim3(64 * MT), lds, stream,
+                           static_cast<const typename E::T *>(p.q),
+                           static_cast<const typename E::T *>(p.k),
+                           static_cast<const typename E::T *>(p.v),
+                           static_cast<typename E::T *>(p.o), a);
+        return;
+    }
     if (p.m == 16 * MT)
         launch_large_f<E, MT, D, true>(p, a, stream);
     else
@@ -790,9 +870,11 @@ void launch_large_e(const Problem &p, const LargeArgs &a, hipStream_t stream)
 
 }  // namespace
 
-bool tiled_large_supported(const Problem &p)
+bool tiled_large_supported(const Problem &p) { return p.N % 16 == 0 && ragged_supported(p); }
+
+bool ragged_supported(const Problem &p)
 {
-    if (p.N % 16 != 0 || p.m > 64 || !tiled_width(p.d))
+    if (p.m > 64 || !tiled_width(p.d))
         return false;
     if (p.dtype == 1) {   // 16-byte row pieces of bf16 need 4-byte aligned rows
         const uintptr_t mis = uintptr_t(p.q) | uintptr_t(p.k) | uintptr_t(p.v);

@@ -1,0 +1,82 @@
+"""Token counts that are not a multiple of 16, through the automatic choice:
+the tiled kernel with a partial last token tile, against the float64 oracle
+and the generic kernel.  Covers one to three landmark-tile counts per residue
+of N mod 32 (a missing second tile, a partial one), single tokens, m = N, both
+landmark modes and values that must not leak from the repeated rows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_08520_amd import binding as B
+from paper_2506_08520_amd import workloads as W
+from helpers import check, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+# (n_windows, heads, N, d, m, mode)
+SHAPES = [
+    (1, 1, 1, 8, 1, 0),       # one token
+    (3, 2, 4, 12, 4, 0),      # m = N, one partial tile
+    (5, 2, 9, 16, 9, 0),
+    (2, 3, 17, 32, 17, 1),    # one token past a tile, two landmark tiles
+    (2, 2, 31, 24, 1, 1),     # one token short of a pair of tiles
+    (2, 2, 33, 30, 11, 1),    # a third tile of one token
+    (3, 2, 36, 30, 9, 0),     # 6 x 6 windows
+    (3, 2, 49, 32, 7, 0),     # 7 x 7: a fourth tile of one token
+    (2, 2, 81, 20, 9, 0),
+    (2, 2, 100, 16, 25, 0),   # 10 x 10: two landmark tiles
+    (1, 2, 196, 28, 49, 0),   # 14 x 14: four landmark tiles
+    (1, 2, 126, 8, 63, 1),
+    (1, 2, 42, 32, 42, 1),    # three landmark tiles, m = N
+    (1, 1, 2025, 30, 25, 0),  # 45 x 45
+    (1, 1, 9999, 16, 33, 1),  # long segments
+    (1, 1, 9604, 32, 49, 0),  # 98 x 98
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_ragged(shape, dtype):
+    nw, h, N, d, m, mode = shape
+    q, k, v = W.iid((nw, h, N, d), seed=N * 17 + d + m, dtype=dtype)
+    ref = oracle.forward(q, k, v, m, iters=6, mode=mode)
+    t = [to_dev(x, dtype) for x in (q, k, v)]
+    got = to_host(B.nystra_attn_forward_ex(*t, m, opts=B.make_opts(landmark_mode=mode)))
+    check(got, ref, dtype, f"ragged {shape} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_neighbours_untouched(dtype):
+    """Rows past a unit's last token are the next unit's: outputs of every unit
+    equal those of the unit computed alone, and the bytes after O stay."""
+    q, k, v = (to_dev(x, dtype) for x in W.iid((7, 1, 49, 30), seed=3, dtype=dtype))
+    pad = 64
+    buf = torch.full((q.numel() + pad,), 7.0, dtype=q.dtype, device="cuda")
+    out = buf[:q.numel()].view(q.shape)
+    B.nystra_attn_forward_ex(q, k, v, 7, out=out)
+    assert (buf[q.numel():] == 7.0).all()
+    for u in (0, 3, 6):
+        alone = B.nystra_attn_forward_ex(q[u:u + 1].contiguous(), k[u:u + 1].contiguous(),
+                                         v[u:u + 1].contiguous(), 7)
+        assert torch.equal(alone[0], out[u])
+
+
+def test_named_variants_unchanged():
+    """AUTO takes the tiled kernel; by name such shapes stay GENERIC only."""
+    assert B.nystra_select_variant(100, 16, 25) == B.VARIANT_GENERIC
+    q = torch.zeros((1, 1, 100, 16), device="cuda")
+    with pytest.raises(B.NystraError):
+        B.nystra_attn_forward_ex(q, q, q, 25, opts=B.make_opts(variant=B.VARIANT_TILED))
+
+
+def test_unaligned_bf16_takes_the_generic_kernel():
+    """bf16 tensors on odd halfwords (not 4-byte aligned) stay accepted."""
+    q, k, v = W.iid((2, 1, 49, 30), seed=9, dtype="bf16")
+    t = []
+    for x in (q, k, v):
+        b = torch.empty(x.size + 1, dtype=torch.bfloat16, device="cuda")
+        b[1:] = to_dev(x, "bf16").view(-1)
+        t.append(b[1:].view(x.shape))
+    got = to_host(B.nystra_attn_forward_ex(*t, 7))
+    check(got, oracle.forward(q, k, v, 7, iters=6, mode=0), "bf16", "ragged, odd halfwords")
