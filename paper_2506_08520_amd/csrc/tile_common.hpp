@@ -122,6 +122,46 @@ __device__ inline void split_bf16(const float (&x)[8], bf8 &hi, bf8 &lo)
     lo = __builtin_bit_cast(bf8, l);
 }
 
+// Eight fp32 values as three bf16 terms, x = h + m + l with |l - (x - h - m)|
+// below 2^-24 |x|: h is x truncated to bf16 (never rounded up to infinity), m
+// and l are rounded to nearest even.  Six of the nine products of two such
+// sums (hh, hm, mh, mm, hl, lh) carry a product to fp32 accuracy; they run as
+// one bf16 matrix instruction each, 96 cycles per 16x16x32 tile against 256 of
+// the fp32 matrix instruction.  An infinity keeps m = l = 0; NaN stays NaN.
+__device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l)
+{
+    const NegSel s = neg_selectors();
+    U16B hw, mw, lw;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        float r[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float v = x[2 * p + e];
+            const float t = __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+            r[e] = fabsf(v) == INFINITY ? 0.f : v - t;
+        }
+        hw.w[p] = __builtin_amdgcn_perm(__float_as_uint(x[2 * p + 1]), __float_as_uint(x[2 * p]),
+                                        0x07060302u);
+        mw.w[p] = cvt_bf16x2(r[0], r[1]);
+        lw.w[p] = residual_bf16x2(mw.w[p], r[0], r[1], s);
+    }
+    h = __builtin_bit_cast(bf8, hw);
+    m = __builtin_bit_cast(bf8, mw);
+    l = __builtin_bit_cast(bf8, lw);
+}
+
+// acc + A B over 32 of the contraction, both as three terms, small products first.
+__device__ inline f4 mfma_split3(bf8 ah, bf8 am, bf8 al, bf8 bh, bf8 bm, bf8 bl, f4 acc)
+{
+    acc = mfma_bf16(al, bh, acc);
+    acc = mfma_bf16(ah, bl, acc);
+    acc = mfma_bf16(am, bm, acc);
+    acc = mfma_bf16(am, bh, acc);
+    acc = mfma_bf16(ah, bm, acc);
+    return mfma_bf16(ah, bh, acc);
+}
+
 __device__ inline SplitTile split_tile(f4 x)
 {
     const NegSel s = neg_selectors();

@@ -164,3 +164,20 @@ def test_block_prepacked_not_needed_past_256_channels():
     assert rc == 0
     torch.cuda.synchronize()
     assert torch.equal(y0, y1)
+
+
+# Past 256 channels: the 128 x 128 tiled GEMM.  Remainders of every tile edge
+# (rows 1 to 200, columns and contraction not multiples of 128, 64 or 32),
+# heads of 8 to 88, and a head width (30) that keeps the kernel it had.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(1, 16, 24, 320, 10, 8, 4, 16), (1, 8, 8, 264, 3, 8, 3, 16),
+                                  (1, 1, 1, 264, 33, 1, 0, 1), (1, 10, 20, 520, 65, 10, 5, 25),
+                                  (2, 8, 16, 512, 16, 8, 0, 16), (1, 8, 8, 300, 10, 8, 4, 16)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_block_past_256_channels(case, dtype):
+    Bn, H, Wd, C, heads, w, s, m = case
+    inputs = W.block_inputs(Bn, H, Wd, C, seed=H * Wd + C, dtype=dtype)
+    ref = OB.block_forward(*inputs, heads=heads, window=w, shift=s, m=m, attention="nystrom",
+                           dtype=dtype, round_output=False)
+    got = run_block(inputs, heads, w, s, m, dtype, "nystrom")
+    check(got, ref, dtype, f"block {case} {dtype}", beyond_bar=BLOCK_BEYOND_BF16)
