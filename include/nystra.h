@@ -260,6 +260,28 @@ int nystra_block_forward_packed(const void *X, const void *Wqkv, const void *bqk
                                 int m, int dtype, const nystra_opts *opts, int attention,
                                 void *workspace, size_t workspace_bytes, void *stream);
 
+/* A whole transformer layer around the block, bf16, channels <= 256:
+ *   x1 = X + block(LayerNorm1(X)),  Y = x1 + W2 gelu(W1 LayerNorm2(x1) + b1) + b2
+ * with the exact (erf) GELU, LayerNorm over the channels with weight and bias.
+ * w1 is [hidden][C] and w2 [C][hidden] (as nn.Linear holds them); b1 and b2 may
+ * be NULL.  `packed` is required (nystra_block_pack_weights); the workspace is
+ * nystra_block_workspace_size's.  x1 and the MLP's sums stay in fp32; the inputs
+ * of every product are rounded to bf16.  channels and hidden must be multiples
+ * of 4 and d_h even, NYSTRA_ERR_UNSUPPORTED otherwise and for fp32; X, Y, w1, w2
+ * 4-byte aligned (NYSTRA_ERR_ALIGN).  Y and the workspace must overlap no input. */
+typedef struct nystra_layer_params {
+    const void *norm1_w, *norm1_b, *norm2_w, *norm2_b, *w1, *b1, *w2, *b2;
+    float eps1, eps2;
+    int hidden;
+} nystra_layer_params;
+
+int nystra_layer_forward(const void *X, const void *Wqkv, const void *bqkv, const void *Wproj,
+                         const void *bproj, const void *packed, size_t packed_bytes,
+                         const nystra_layer_params *layer, void *Y,
+                         const nystra_block_shape *shape, int m, int dtype,
+                         const nystra_opts *opts, int attention, void *workspace,
+                         size_t workspace_bytes, void *stream);
+
 /* Exact windowed softmax self-attention, Eq. (1), per unit:
  *   O = softmax(scale Q K^T) V, with the row maximum subtracted inside the
  *   softmax.  scale <= 0 selects 1/sqrt(d_h).  Same layout, limits and

@@ -24,7 +24,7 @@ EXPORTS = (
     "nystra_select_variant", "nystra_attn_workspace_size", "nystra_attn_forward_ws",
     "nystra_block_workspace_size", "nystra_block_forward", "nystra_attn_forward_noalloc",
     "nystra_block_packed_size", "nystra_block_pack_weights", "nystra_block_forward_packed",
-    "nystra_status_str", "nystra_last_error",
+    "nystra_layer_forward", "nystra_status_str", "nystra_last_error",
 )
 STATIC_SCRATCH_BYTES = 32 << 20   # NYSTRA_STATIC_SCRATCH_BYTES
 BLOCK_NYSTROM, BLOCK_EXACT = 0, 1
@@ -44,6 +44,12 @@ class NystraError(RuntimeError):
 class BlockShape(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("batch", "height", "width", "channels", "heads",
                                               "window", "shift")]
+
+
+class LayerParams(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_void_p) for n in ("norm1_w", "norm1_b", "norm2_w", "norm2_b",
+                                                "w1", "b1", "w2", "b2")] +
+                [("eps1", ctypes.c_float), ("eps2", ctypes.c_float), ("hidden", ctypes.c_int)])
 
 
 class Opts(ctypes.Structure):
@@ -94,6 +100,10 @@ def lib():
                                                            ctypes.POINTER(BlockShape), _i, _i,
                                                            ctypes.POINTER(Opts), _i, _vp,
                                                            ctypes.c_size_t, _vp])
+    L.nystra_layer_forward.argtypes = ([_vp] * 6 + [ctypes.c_size_t, ctypes.POINTER(LayerParams),
+                                                    _vp, ctypes.POINTER(BlockShape), _i, _i,
+                                                    ctypes.POINTER(Opts), _i, _vp,
+                                                    ctypes.c_size_t, _vp])
     for name in EXPORTS:
         if name not in ("nystra_status_str", "nystra_last_error"):
             getattr(L, name).restype = ctypes.c_int
@@ -251,6 +261,46 @@ def nystra_block_forward(x, w_qkv, b_qkv, w_proj, b_proj, heads, window, shift=0
                                                ctypes.byref(shape), m, code, po, attention,
                                                _ptr(workspace), nbytes, _stream(stream))
         _check(rc, "nystra_block_forward_packed")
+    return y
+
+
+def nystra_layer_forward(x, w_qkv, b_qkv, w_proj, b_proj, packed, norm1, norm2, w1, b1, w2, b2,
+                         heads, window, shift=0, m=16, opts=None, attention=BLOCK_NYSTROM,
+                         workspace=None, stream=None):
+    """Transformer layer on x [B, H, W, C] (bf16, device, contiguous): the block
+    between LayerNorm and residual, then LayerNorm, MLP and residual.  ``norm1``
+    and ``norm2`` are (weight, bias, eps); ``w1`` [hidden, C] and ``w2``
+    [C, hidden] as nn.Linear holds them; ``packed`` from
+    nystra_block_pack_weights."""
+    import torch
+    if x.dim() != 4 or not x.is_contiguous() or not x.is_cuda:
+        raise ValueError("x must be a contiguous device tensor [B, H, W, C]")
+    C, hidden = int(x.shape[-1]), int(w1.shape[0])
+    if tuple(w1.shape) != (hidden, C) or tuple(w2.shape) != (C, hidden):
+        raise ValueError("expected w1 [hidden, C] and w2 [C, hidden]")
+    sizes = ((w_qkv, 3 * C * C), (b_qkv, 3 * C), (w_proj, C * C), (b_proj, C), (w1, hidden * C),
+             (b1, hidden), (w2, hidden * C), (b2, C), (norm1[0], C), (norm1[1], C),
+             (norm2[0], C), (norm2[1], C))
+    for t, n in sizes:
+        if t is not None and (t.dtype != x.dtype or t.numel() != n or not t.is_contiguous() or
+                              t.device != x.device):
+            raise ValueError("weights must be contiguous tensors of x's dtype and device")
+    shape = BlockShape(*(int(v) for v in x.shape), heads, window, shift)
+    code = _dtype_code(x)
+    need = nystra_block_workspace_size(shape, m, code, opts, attention)
+    if workspace is None and need > 0:
+        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
+    nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    pk = packed.numel() * packed.element_size() if packed is not None else 0
+    y = torch.empty_like(x)
+    lp = LayerParams(*(_ptr(t) for t in (*norm1[:2], *norm2[:2], w1, b1, w2, b2)),
+                     float(norm1[2]), float(norm2[2]), hidden)
+    po = ctypes.byref(opts) if opts is not None else None
+    rc = lib().nystra_layer_forward(_ptr(x), _ptr(w_qkv), _ptr(b_qkv), _ptr(w_proj), _ptr(b_proj),
+                                    _ptr(packed), pk, ctypes.byref(lp), _ptr(y),
+                                    ctypes.byref(shape), m, code, po, attention, _ptr(workspace),
+                                    nbytes, _stream(stream))
+    _check(rc, "nystra_layer_forward")
     return y
 
 

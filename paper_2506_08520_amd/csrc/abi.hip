@@ -555,17 +555,23 @@ size_t packed_parts(int C, int dtype, size_t *qkv_part)
 
 // The block of nystra_block_forward.  With with_packed, the GEMMs read the
 // weight image at `packed` (required when channels <= 256, ignored above)
-// instead of packing W_qkv and W_proj into the workspace first.
+// instead of packing W_qkv and W_proj into the workspace first.  With `layer`, a
+// whole transformer layer: the QKV product normalises its rows, and the tail
+// kernel takes the place of the PROJ product.
 int block_forward(const void *X, const void *Wqkv, const void *bqkv, const void *Wproj,
                   const void *bproj, bool with_packed, const void *packed,
                   size_t packed_bytes, void *Y,
                   const nystra_block_shape *shape, int m, int dtype, const nystra_opts *opts,
-                  int attention, void *workspace, size_t workspace_bytes, void *stream)
+                  int attention, void *workspace, size_t workspace_bytes, void *stream,
+                  const nystra_layer_params *layer = nullptr)
 {
     BlockPlan bp;
     int rc = plan_block(shape, m, dtype, opts, attention, &bp);
     if (rc != NYSTRA_OK)
         return rc;
+    if (layer && !nystra::layer_supported(int64_t(shape->batch) * shape->height * shape->width,
+                                          shape->channels, shape->heads, dtype, layer->hidden))
+        return NYSTRA_ERR_UNSUPPORTED;
     if (shape->batch == 0)
         return NYSTRA_OK;
     const bool use_packed = with_packed && bp.pk_qkv != 0;
@@ -596,6 +602,28 @@ int block_forward(const void *X, const void *Wqkv, const void *bqkv, const void 
             return NYSTRA_ERR_ALIGN;
         if (overlaps(packed, pb, Y, xb) || overlaps(packed, pb, workspace, wsb))
             return NYSTRA_ERR_OVERLAP;
+    }
+    if (layer) {   // four-byte pieces of X, the MLP weights and Y
+        const int64_t hb = int64_t(layer->hidden) * eb, cb = int64_t(C) * eb;
+        const struct { const void *p; int64_t n; int align; bool need; } t[] = {
+            {layer->norm1_w, cb, eb, true}, {layer->norm1_b, cb, eb, true},
+            {layer->norm2_w, cb, eb, true}, {layer->norm2_b, cb, eb, true},
+            {layer->w1, hb * C, 4, true},   {layer->b1, hb, eb, false},
+            {layer->w2, hb * C, 4, true},   {layer->b2, cb, eb, false},
+            {X, xb, 4, true},               {Y, 0, 4, true}};
+        for (const auto &x : t) {
+            if (!x.p) {
+                if (x.need)
+                    return NYSTRA_ERR_NULL;
+                continue;
+            }
+            if (misaligned(x.p, x.align))
+                return NYSTRA_ERR_ALIGN;
+            if (x.n && overlaps(Y, xb, x.p, x.n))
+                return NYSTRA_ERR_OVERLAP;
+            if (x.n && overlaps(workspace, wsb, x.p, x.n))
+                return NYSTRA_ERR_WORKSPACE;
+        }
     }
     char *ws = static_cast<char *>(workspace);
     void *q = ws, *k = ws + bp.qkvo_bytes, *v = ws + 2 * bp.qkvo_bytes,
@@ -632,6 +660,11 @@ int block_forward(const void *X, const void *Wqkv, const void *bqkv, const void 
     g.out0 = q;
     g.out1 = k;
     g.out2 = v;
+    if (layer) {
+        g.lnw = layer->norm1_w;
+        g.lnb = layer->norm1_b;
+        g.eps = layer->eps1;
+    }
     hipError_t e = nystra::launch_block_gemm(g, st);
     if (e != hipSuccess)
         return finish_launch(e);
@@ -655,6 +688,20 @@ int block_forward(const void *X, const void *Wqkv, const void *bqkv, const void 
     g.bias = bproj;
     g.out0 = Y;
     g.out1 = g.out2 = nullptr;
+    if (layer) {
+        nystra::LayerTail t;
+        t.gemm = g;
+        t.x = X;
+        t.lnw = layer->norm2_w;
+        t.lnb = layer->norm2_b;
+        t.w1 = layer->w1;
+        t.b1 = layer->b1;
+        t.w2 = layer->w2;
+        t.b2 = layer->b2;
+        t.eps = layer->eps2;
+        t.hidden = layer->hidden;
+        return finish_launch(nystra::launch_layer_tail(t, st));
+    }
     return finish_launch(nystra::launch_block_gemm(g, st));
 }
 
@@ -733,6 +780,21 @@ int nystra_block_forward_packed(const void *X, const void *Wqkv, const void *bqk
 {
     return block_forward(X, Wqkv, bqkv, Wproj, bproj, true, packed, packed_bytes, Y, shape, m,
                          dtype, opts, attention, workspace, workspace_bytes, stream);
+}
+
+int nystra_layer_forward(const void *X, const void *Wqkv, const void *bqkv, const void *Wproj,
+                         const void *bproj, const void *packed, size_t packed_bytes,
+                         const nystra_layer_params *layer, void *Y,
+                         const nystra_block_shape *shape, int m, int dtype,
+                         const nystra_opts *opts, int attention, void *workspace,
+                         size_t workspace_bytes, void *stream)
+{
+    if (!layer)
+        return NYSTRA_ERR_NULL;
+    if (!isfinite(layer->eps1) || !isfinite(layer->eps2))
+        return NYSTRA_ERR_ARG;
+    return block_forward(X, Wqkv, bqkv, Wproj, bproj, true, packed, packed_bytes, Y, shape, m,
+                         dtype, opts, attention, workspace, workspace_bytes, stream, layer);
 }
 
 const char *nystra_status_str(int status)

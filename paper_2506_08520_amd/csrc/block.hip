@@ -14,8 +14,7 @@
 // current one is multiplied; four waves each own a 32 x 32 quarter (2 x 2
 // MFMA tiles).  Blocks are mapped so that the column tiles of one row tile
 // run on the same XCD and share its L2 for the gathered rows.
-#include "internal.hpp"
-#include "tile_common.hpp"
+#include "block_common.hpp"
 
 namespace nystra {
 namespace {
@@ -23,36 +22,6 @@ namespace {
 using namespace tile;
 
 constexpr int kBM = 64, kBN = 64, kBK = 32;
-
-struct BlockArgs {
-    int64_t rows;                 // tokens, B H W
-    int H, W, C, heads, dh, w, N, shift, nwx, nwy;
-    int ncols;                    // 3C (QKV) or C (PROJ)
-    int rtiles, ctiles;           // tile grid
-    const void *a;                // X (QKV) or O (PROJ)
-    const void *wt;               // [C][ncols]
-    const void *wpk;              // wt packed as the register-resident kernel's LDS tiles
-    const void *bias;             // [ncols] or null
-    void *out0, *out1, *out2;     // Q, K, V (QKV) or Y (PROJ)
-    bool pair;                    // register-resident kernel: store adjacent column pairs
-    int64_t ostride;              // register-resident kernel: elements from Q to K and K to V
-};
-
-// Flat pixel (b H + y) W + x of token t of window `win`.
-__device__ inline int64_t pixel_of(const BlockArgs &a, int64_t win, int t)
-{
-    const int per = a.nwy * a.nwx;
-    const int64_t b = win / per;
-    const int wi = int(win - b * per);
-    const int wy = wi / a.nwx, wx = wi - wy * a.nwx;
-    const int ty = t / a.w, tx = t - ty * a.w;
-    int y = wy * a.w + ty + a.shift, x = wx * a.w + tx + a.shift;
-    if (y >= a.H)
-        y -= a.H;
-    if (x >= a.W)
-        x -= a.W;
-    return (b * a.H + y) * a.W + x;
-}
 
 // Block id -> (row tile, column tile), so that consecutive logical tiles (the
 // column tiles of one row tile) land on one XCD (ids go round-robin over 8).
@@ -63,12 +32,6 @@ __device__ inline void tile_of(const BlockArgs &a, int &rt, int &ct)
     const int L = (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + local;
     rt = L / a.ctiles;
     ct = L - rt * a.ctiles;
-}
-
-template <class E>
-__device__ inline float ld(const void *p, int64_t i)
-{
-    return E::load(static_cast<const typename E::T *>(p), i);
 }
 
 template <class E, bool PROJ>
@@ -460,32 +423,24 @@ bool wide_ok(const BlockArgs &a, bool proj)
 }
 
 // Register-resident variant for C <= 256 (K padded to KP, a multiple of 32).
-// Each wave holds its 16 rows of A for the whole contraction in registers, in
-// the operand layout of the matrix cores: lane group g takes the contiguous
-// quarter k in [g KP/4, (g+1) KP/4), so A is read from memory exactly once.
-// The workgroup's eight waves (128 rows) stream W through LDS one 64-column
-// tile at a time, double-buffered: the next tile's loads are in flight while
-// the current one is multiplied.  W tiles in LDS: fp32 as [k][c][t] (the four
-// 16-column tiles' values of column c side by side, one 16-byte read per
-// step), bf16 transposed as [n][k] (eight k per 16-byte read).
-constexpr int kRkWaves = 8, kRkRows = 16 * kRkWaves;
-
-template <class E, int KP>
-struct RkLds {
-    static constexpr bool BF = E::bytes == 2;
-    static constexpr int PF = 68;            // fp32 [k][c][t]: 64 floats + 4 per k
-    static constexpr int PH = KP + 8;        // bf16 [n][k]: halves per column
-    static constexpr int tile = BF ? 64 * PH / 2 : KP * PF;   // floats per buffer
-    static constexpr int astage = 16 * 8 * (KP / (BF ? 2 : 1) + 8);   // 128 rows, words
-    static constexpr int total = 2 * tile > astage ? 2 * tile : astage;
-};
-
-// Packs W [C][ncols] into the LDS images of its 64-column tiles, one tile
-// after another: bf16 [n][k] with pitch PH (element (k, n0 + n) at n PH + k),
-// fp32 [k][PF] with the four 16-column tiles' values of column c at 4c + t
-// (element (k, n0 + 16t + c)).  Every slot outside W (k >= C, n >= ncols, the
-// pitch padding) is zero.  The second matrix's pieces follow the first's in
-// the grid.
+// Each wave holds its RT row tiles of A for the whole contraction in
+// registers, in the operand layout of the matrix cores: lane group g takes the
+// contiguous quarter k in [g KP/4, (g+1) KP/4), so A is read from memory exactly
+// once.  The workgroup's waves (128 rows) stream W through LDS one tile of
+// CT columns at a time, double-buffered: the next tile's loads are in flight
+// while the current one is multiplied.  W tiles in LDS: transposed bf16, [n][k]
+// (eight k per 16-byte read); fp32 operands are carried as three bf16 terms
+// (mfma_split3), A split once into registers, W on the way into LDS, a tile
+// there holding the three planes one after another.
+// LDS reads bound the loop: a W operand read (8 cycles of the CU's LDS, 32 for
+// its four SIMDs) feeds RT matrix instructions of 16 cycles (96 in fp32), so two
+// row tiles a wave halve the LDS time of one.  CT is the widest tile that lets
+// two workgroups share a CU's 160 KB.
+// MEASURED_RK
+// Packs W [C][ncols], transposed, by 64-column tiles, one after another: [n][k]
+// with pitch PH halves (bf16, the tile's LDS image) or KP floats.  Every slot
+// outside W (k >= C, n >= ncols, the pitch padding) is zero.  The second matrix's
+// pieces follow the first's in the grid.
 struct WPackArgs {
     const void *w0, *w1;   // W_qkv [C][3C], W_proj [C][C]
     uint32_t *d0, *d1;     // their packed images
@@ -495,10 +450,9 @@ struct WPackArgs {
 template <class E, int KP>
 __global__ void __launch_bounds__(256) block_wpack_kernel(WPackArgs p)
 {
-    // One thread per 16-byte piece of the images (four words).
+    // One thread per 16-byte piece: eight (bf16) or four (fp32) k of a column.
     using L = RkLds<E, KP>;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int kPieces = L::tile / 4;   // per tile
+    constexpr int kPieces = L::image / 4, EP = E::bytes == 2 ? 8 : 4;
     const int64_t gi = int64_t(blockIdx.x) * 256 + threadIdx.x;
     const int64_t p0 = p.words0 / 4;
     const bool second = gi >= p0;
@@ -508,73 +462,69 @@ __global__ void __launch_bounds__(256) block_wpack_kernel(WPackArgs p)
     const int ncols = second ? p.C : 3 * p.C;
     const typename E::T *W = static_cast<const typename E::T *>(second ? p.w1 : p.w0);
     const int ct = int(pi / kPieces), r = int(pi - int64_t(ct) * kPieces), n0 = 64 * ct;
-    // Branch-free: every load reads an in-bounds element (indices clamped) and
-    // a select zeroes the slots outside W, so a thread's loads issue together.
-    auto elem = [&](int k, int n) -> uint32_t {
-        const bool ok = k < p.C && n < ncols;
-        const int64_t i = int64_t(k < p.C ? k : p.C - 1) * ncols + (n < ncols ? n : ncols - 1);
-        uint32_t x;
+    // column n = r mod 64 (consecutive threads: consecutive columns of EP rows
+    // of W), elements k0 .. k0 + EP - 1 of its image row.  Branch-free: every
+    // load reads an in-bounds element (indices clamped) and a select zeroes the
+    // slots outside W, so a thread's loads issue together.
+    const int n = r & 63, k0 = EP * (r >> 6);
+    uint32_t x[EP];
+#pragma unroll
+    for (int e = 0; e < EP; ++e) {
+        const int k = k0 + e;
+        const bool ok = k < p.C && n0 + n < ncols;
+        const int64_t i = int64_t(k < p.C ? k : p.C - 1) * ncols + (n0 + n < ncols ? n0 + n : ncols - 1);
+        uint32_t w;
         if constexpr (E::bytes == 2)
-            x = uint32_t(reinterpret_cast<const uint16_t *>(W)[i]);
+            w = uint32_t(reinterpret_cast<const uint16_t *>(W)[i]);
         else
-            x = __float_as_uint(W[i]);
-        return ok ? x : 0u;
-    };
+            w = __float_as_uint(W[i]);
+        x[e] = ok ? w : 0u;
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 out;
     int dst;   // piece index within the tile image
     if constexpr (E::bytes == 2) {
-        // column n = r mod 64 (consecutive threads: consecutive columns of
-        // eight rows of W), halves k0 .. k0 + 7 of its image row
-        const int n = r & 63, k0 = 8 * (r >> 6);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = k0 + 2 * e;
-            out[e] = elem(k, n0 + n) | (elem(k + 1, n0 + n) << 16);   // zero from k = C on
-        }
+        for (int e = 0; e < 4; ++e)
+            out[e] = x[2 * e] | (x[2 * e + 1] << 16);
         dst = (n * L::PH + k0) / 8;
     } else {
-        // row k, column c: the four 16-column tiles' values (slot 16 of a row
-        // is the pitch padding)
-        const int k = r / (L::PF / 4), c = r - k * (L::PF / 4);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-            out[t] = c < 16 ? elem(k, n0 + 16 * t + c) : 0u;
-        dst = r;
+        for (int e = 0; e < 4; ++e)
+            out[e] = x[e];
+        dst = k0 < KP ? (n * KP + k0) / 4 : r;   // past the rows: the unused words
     }
     reinterpret_cast<u32x4 *>(second ? p.d1 : p.d0)[int64_t(ct) * kPieces + dst] = out;
 }
 
-// Words per batch of the A stage: the largest divisor of n up to 16.
-constexpr int stage_batch(int n)
-{
-    for (int b = 16; b > 1; --b)
-        if (n % b == 0)
-            return b;
-    return 1;
-}
-
-template <class E, bool PROJ, int KP>
-__global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs a)
+// LN (bf16, QKV): the rows of A are normalised (LayerNorm over C, affine) once
+// they are in registers -- a row's quarters lie in the four lane groups, so its
+// sums take two cross-lane steps -- and rounded to bf16 as the norm's own output
+// would be: the map is neither written nor read in between.
+template <class E, bool PROJ, int KP, bool LN = false>
+__global__ void __launch_bounds__(rk_threads<E>()) 
+__attribute__((amdgpu_waves_per_eu(E::bytes == 4 || LN ? 2 : 4)))
+block_gemm_rk_kernel(BlockArgs a)
 {
     constexpr bool BF = E::bytes == 2;
     using L = RkLds<E, KP>;
     constexpr int KQ = KP / 4;               // contraction slots per lane group
+    constexpr int RT = rk_rt<E>(), NQ = L::CT / 16, kRkThreads = rk_threads<E>();
     __shared__ __align__(16) float lds_all[L::total];
     auto wbuf = [&](int b) { return lds_all + b * L::tile; };
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t m0 = int64_t(blockIdx.x) * kRkRows;
 
-    // ---- A: the workgroup's 128 rows are staged in LDS with coalesced 4-byte
-    // loads (lanes take consecutive words of a row; bf16 words hold two
-    // elements), then each lane copies its operand slots -- row 16 wv + c,
-    // k = g KQ + s -- into registers.  The stage shares LDS with the W tiles.
+    // ---- A: the workgroup's 128 rows are staged in LDS, SR at a time, with
+    // coalesced 4-byte loads (lanes take consecutive words of a row; bf16 words
+    // hold two elements), then each lane copies its operand slots -- rows
+    // 16 (RT wv + rt) + c, k = g KQ + s -- into registers.  The stage and its
+    // offset tables share LDS with the W tiles.
     constexpr int EPW = BF ? 2 : 1;              // elements per 4-byte word
-    constexpr int AWL = KP / EPW;                // words per staged row
-    constexpr int AP = AWL + 8;                  // row pitch (words; + 8: fewer bank conflicts
-                                                 // than + 4 in the operand reads)
-    __shared__ int rowbase[kRkRows];             // element offset of row r (-1: none)
-    __shared__ int colofs[AWL];                  // element offset of word w in a row
+    constexpr int AWL = L::AWL, AP = L::AP;
+    int *rowbase = reinterpret_cast<int *>(lds_all + L::rowbase);   // row r's element offset (-1: none)
+    int *colofs = reinterpret_cast<int *>(lds_all + L::colofs);     // word w's offset in a row
     float *astage = lds_all;
     if (tid < kRkRows) {
         const int64_t row = m0 + tid;
@@ -586,7 +536,14 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
         }
         rowbase[tid] = base;
     }
-    for (int w = tid; w < AWL; w += 64 * kRkWaves) {
+    __shared__ float lnt[LN ? 2 * KP : 1];   // weight and bias of the norm, zero from C on
+    if constexpr (LN) {
+        for (int k = tid; k < KP; k += kRkThreads) {
+            lnt[k] = k < a.C ? ld<E>(a.lnw, k) : 0.f;
+            lnt[KP + k] = k < a.C ? ld<E>(a.lnb, k) : 0.f;
+        }
+    }
+    for (int w = tid; w < AWL; w += kRkThreads) {
         const int k = w * EPW;
         int off = k;
         if constexpr (PROJ) {
@@ -595,32 +552,46 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
         }
         colofs[w] = k < a.C ? off : -1;
     }
-    // ---- W tiles: the packed image of each 64-column tile (block_wpack_kernel
-    // lays it out exactly as the LDS tile below, padding included) is copied
-    // global -> registers -> LDS in 16-byte pieces, consecutive lanes taking
-    // consecutive pieces: coalesced loads, conflict-free stores, no index
-    // arithmetic per element.
+    // ---- W tiles: the packed image of a tile goes global -> registers -> LDS
+    // in 16-byte pieces.  bf16: the image is the LDS tile, padding included, so
+    // consecutive lanes copy consecutive pieces.  fp32: a thread takes eight k
+    // of a column (two pieces), splits them and stores one piece per plane.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int kPieces = L::tile / 4;   // 16-byte pieces of a tile image
-    constexpr int kPer = (kPieces + 64 * kRkWaves - 1) / (64 * kRkWaves);
-    u32x4 wr[kPer];
-    const int nct = (a.ncols + 63) / 64;
+    constexpr int kPieces = BF ? L::tile / 4 : L::CT * KP / 8;
+    constexpr int kPer = (kPieces + kRkThreads - 1) / kRkThreads;
+    constexpr int WPP = BF ? 1 : 2;        // loads per piece
+    u32x4 wr[kPer][WPP];
+    const int nct = (a.ncols + L::CT - 1) / L::CT;
     const u32x4 *wsrc = static_cast<const u32x4 *>(a.wpk);
     auto wfetch = [&](int ct) {
-        const u32x4 *src = wsrc + int64_t(ct) * kPieces;
+        constexpr int per = 64 / L::CT;    // tiles per 64-column image
+        const u32x4 *src = wsrc + int64_t(ct / per) * (L::image / 4) + (ct % per) * kPieces * WPP;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {   // past the image: re-read its last piece
-            const int idx = tid + j * 64 * kRkWaves;
-            wr[j] = src[idx < kPieces ? idx : kPieces - 1];
+            const int idx = tid + j * kRkThreads;
+#pragma unroll
+            for (int h = 0; h < WPP; ++h)
+                wr[j][h] = src[(idx < kPieces ? idx : kPieces - 1) * WPP + h];
         }
     };
     auto wstash = [&](int buf) {
         u32x4 *dst = reinterpret_cast<u32x4 *>(wbuf(buf));
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-            const int idx = tid + j * 64 * kRkWaves;
-            if (kPer * 64 * kRkWaves == kPieces || idx < kPieces)
-                dst[idx] = wr[j];
+            const int idx = tid + j * kRkThreads;
+            if (kPer * kRkThreads == kPieces || idx < kPieces) {
+                if constexpr (BF) {
+                    dst[idx] = wr[j][0];
+                } else {
+                    float x[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = __uint_as_float(wr[j][e / 4][e % 4]);
+                    const int n = idx / (KP / 8), kp = idx - n * (KP / 8);
+                    bf8 *d = reinterpret_cast<bf8 *>(dst) + n * (L::PH / 8) + kp;
+                    split3_bf16(x, d[0], d[L::plane / 4], d[2 * (L::plane / 4)]);
+                }
+            }
         }
     };
     // Workgroups start at different column tiles, so that at any moment they
@@ -632,74 +603,120 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
     // global load in the epilogue would wait behind the next tile's W pieces
     // in flight).
     wfetch(phys(0));
-    __shared__ float colbias[3 * 256];
-    constexpr int kBiasPer = (3 * 256 + 64 * kRkWaves - 1) / (64 * kRkWaves);
+    __shared__ float colbias[3 * KP];
+    constexpr int kBiasPer = (3 * KP + kRkThreads - 1) / kRkThreads;
     float bz[kBiasPer];
 #pragma unroll
     for (int j = 0; j < kBiasPer; ++j) {
-        const int n = tid + j * 64 * kRkWaves;
+        const int n = tid + j * kRkThreads;
         const int nc = n < a.ncols ? n : a.ncols - 1;
         bz[j] = a.bias ? ld<E>(a.bias, nc) : 0.f;
     }
-    __syncthreads();
-    {
+    bf8 ab[RT][L::NP][KQ / 8];
+    const uint32_t *asrc = static_cast<const uint32_t *>(a.a);
+    uint32_t *adst = reinterpret_cast<uint32_t *>(astage);
+#pragma unroll
+    for (int ph = 0; ph < kRkRows / L::SR; ++ph) {
+        __syncthreads();   // the tables are complete; the last stage has been read
         // Each thread copies kPerT words, in batches whose loads are all in
         // flight before the first is waited for (a loop of load, wait, store
         // would chain kPerT memory round trips).
-        constexpr int kPerT = kRkRows * AWL / (64 * kRkWaves);
+        constexpr int kPerT = L::SR * AWL / kRkThreads;
         constexpr int kBatch = stage_batch(kPerT);
-        static_assert(kPerT * 64 * kRkWaves == kRkRows * AWL, "whole words per thread");
-        const uint32_t *src = static_cast<const uint32_t *>(a.a);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(astage);
+        static_assert(kPerT * kRkThreads == L::SR * AWL, "whole words per thread");
         for (int b0 = 0; b0 < kPerT; b0 += kBatch) {
             uint32_t x[kBatch];
-            int at[kBatch];
+            bool ok[kBatch];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const int j = tid + (b0 + u) * 64 * kRkWaves;
+                const int j = tid + (b0 + u) * kRkThreads;
                 const int row = j / AWL, w = j - row * AWL;
-                const int rb = rowbase[row], co = colofs[w];
-                const bool ok = rb >= 0 && co >= 0;
-                const int e = ok ? rb + co : 0;
-                x[u] = src[BF ? e >> 1 : e];
-                at[u] = ok ? row * AP + w : -1;
+                const int rb = rowbase[ph * L::SR + row], co = colofs[w];
+                ok[u] = rb >= 0 && co >= 0;
+                const int e = ok[u] ? rb + co : 0;
+                x[u] = asrc[BF ? e >> 1 : e];
             }
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const int j = tid + (b0 + u) * 64 * kRkWaves;
+                const int j = tid + (b0 + u) * kRkThreads;
                 const int row = j / AWL, w = j - row * AWL;
-                dst[row * AP + w] = at[u] >= 0 ? x[u] : 0u;
+                adst[row * AP + w] = ok[u] ? x[u] : 0u;
+            }
+        }
+        __syncthreads();
+        if (16 * RT * wv / L::SR == ph) {   // uniform: this wave's rows
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const float *arow = astage + (16 * RT * wv % L::SR + 16 * rt + c) * AP;
+#pragma unroll
+                for (int s = 0; s < KQ / 8; ++s) {
+                    if constexpr (BF) {
+                        ab[rt][0][s] = *reinterpret_cast<const bf8 *>(arow + (g * KQ + 8 * s) / 2);
+                    } else {
+                        const f4 lo = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s);
+                        const f4 hi = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s + 4);
+                        const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                        split3_bf16(x, ab[rt][0][s], ab[rt][L::NP / 2][s], ab[rt][L::NP - 1][s]);
+                    }
+                }
             }
         }
     }
-    __syncthreads();
-    float av[BF ? 1 : KQ];
-    bf8 ab[BF ? KQ / 8 : 1];
-    {
-        const float *arow = astage + (16 * wv + c) * AP;
-        if constexpr (BF) {
+    if constexpr (LN) {
+        static_assert(BF && RT == 1, "LayerNorm in the prologue: bf16");
+        // The rows stay packed between the three passes over them: without
+        // this the unpacked values of the first pass are kept, and spilled.
+        auto keep_packed = [&]() {
 #pragma unroll
             for (int s = 0; s < KQ / 8; ++s)
-                ab[s] = *reinterpret_cast<const bf8 *>(arow + (g * KQ + 8 * s) / 2);
-        } else {
+                asm volatile("" : "+v"(ab[0][0][s]));
+        };
+        float sum = 0.f, sq = 0.f;
 #pragma unroll
-            for (int s = 0; s < KQ; s += 4) {
-                const f4 v = *reinterpret_cast<const f4 *>(arow + g * KQ + s);
+        for (int s = 0; s < KQ / 8; ++s) {
+            float f[8];
+            unpack_bf8(ab[0][0][s], f);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    av[s + e] = v[e];
+            for (int e = 0; e < 8; ++e)
+                sum += f[e];   // zero from k = C on
+        }
+        const float mean = sum_groups(sum) / float(a.C);
+        keep_packed();
+#pragma unroll
+        for (int s = 0; s < KQ / 8; ++s) {
+            float f[8];
+            unpack_bf8(ab[0][0][s], f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float d = g * KQ + 8 * s + e < a.C ? f[e] - mean : 0.f;
+                sq = fmaf(d, d, sq);
             }
+        }
+        const float rstd = 1.f / sqrtf(sum_groups(sq) / float(a.C) + a.eps);
+        keep_packed();
+#pragma unroll
+        for (int s = 0; s < KQ / 8; ++s) {
+            float f[8];
+            unpack_bf8(ab[0][0][s], f);
+            const float *lw = lnt + g * KQ + 8 * s, *lb = lw + KP;
+            U16B u;
+#pragma unroll
+            for (int p = 0; p < 4; ++p)   // weight and bias are zero from C on
+                u.w[p] = cvt_bf16x2(fmaf((f[2 * p] - mean) * rstd, lw[2 * p], lb[2 * p]),
+                                    fmaf((f[2 * p + 1] - mean) * rstd, lw[2 * p + 1], lb[2 * p + 1]));
+            ab[0][0][s] = __builtin_bit_cast(bf8, u);
+            __builtin_amdgcn_sched_barrier(0);   // few table reads in flight: registers
         }
     }
     __syncthreads();   // the stage becomes the W tiles
 
-    // Column part of the destination for the 64 columns of the current tile,
+    // Column part of the destination for the columns of the current tile,
     // from out0: (QKV) output tensor `which` at which * ostride, head h,
     // feature f -> h N d_h + f; (PROJ) the column.
-    __shared__ uint32_t coltab[2][64];
+    __shared__ uint32_t coltab[2][L::CT];
     auto cfill = [&](int ct, int buf) {
-        if (tid < 64) {
-            const int n = 64 * ct + tid;
+        if (tid < L::CT) {
+            const int n = L::CT * ct + tid;
             int which = 0, col = n;
             if constexpr (!PROJ) {
                 which = n / a.C;
@@ -715,21 +732,23 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
     // (window wn, token tt) -> wn N C + tt d_h; PROJ -> pixel C.  Offsets are
     // unsigned 32-bit (tensors under 2^31 elements); rows past the end are
     // not stored.
-    uint32_t rowoff[4];
-    bool rowok[4];
+    uint32_t rowoff[RT][4];
+    bool rowok[RT][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = int(m0) + 16 * wv + 4 * g + i;   // rows < 2^31
-        rowok[i] = row < a.rows;
-        const int rr = rowok[i] ? row : 0;
-        const int wn = rr / a.N, tt = rr - wn * a.N;
-        rowoff[i] = uint32_t(PROJ ? pixel_of(a, wn, tt) * a.C
-                                  : int64_t(wn) * a.N * a.C + int64_t(tt) * a.dh);
-    }
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = int(m0) + 16 * (RT * wv + rt) + 4 * g + i;   // rows < 2^31
+            rowok[rt][i] = row < a.rows;
+            const int rr = rowok[rt][i] ? row : 0;
+            const int wn = rr / a.N, tt = rr - wn * a.N;
+            rowoff[rt][i] = uint32_t(PROJ ? pixel_of(a, wn, tt) * a.C
+                                          : int64_t(wn) * a.N * a.C + int64_t(tt) * a.dh);
+        }
 
 #pragma unroll
     for (int j = 0; j < kBiasPer; ++j) {
-        const int n = tid + j * 64 * kRkWaves;
+        const int n = tid + j * kRkThreads;
         if (n < a.ncols)
             colbias[n] = bz[j];
     }
@@ -742,29 +761,32 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
         if (more)
             wfetch(phys(it + 1));
         const float *wt = wbuf(it & 1);
-        f4 acc[4];
+        f4 acc[RT][NQ];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (BF) {
-            const uint16_t *h = reinterpret_cast<const uint16_t *>(wt);
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int s = 0; s < KQ / 8; ++s)
+            for (int q = 0; q < NQ; ++q)
+                acc[rt][q] = f4{0.f, 0.f, 0.f, 0.f};
+        const uint16_t *h = reinterpret_cast<const uint16_t *>(wt);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const bf8 bv = *reinterpret_cast<const bf8 *>(
-                        &h[(16 * q + c) * L::PH + g * KQ + 8 * s]);
-                    acc[q] = mfma_bf16(ab[s], bv, acc[q]);
+        for (int s = 0; s < KQ / 8; ++s)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                bf8 bv[L::NP];
+#pragma unroll
+                for (int p = 0; p < L::NP; ++p)
+                    bv[p] = *reinterpret_cast<const bf8 *>(
+                        &h[2 * p * L::plane + (16 * q + c) * L::PH + g * KQ + 8 * s]);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    if constexpr (BF)
+                        acc[rt][q] = mfma_bf16(ab[rt][0][s], bv[0], acc[rt][q]);
+                    else
+                        acc[rt][q] = mfma_split3(ab[rt][0][s], ab[rt][L::NP / 2][s],
+                                                 ab[rt][L::NP - 1][s], bv[0], bv[L::NP / 2],
+                                                 bv[L::NP - 1], acc[rt][q]);
                 }
-        } else {
-#pragma unroll
-            for (int s = 0; s < KQ; ++s) {
-                const f4 bv = *reinterpret_cast<const f4 *>(&wt[(g * KQ + s) * L::PF + 4 * c]);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc[q] = mfma4(av[s], bv[q], acc[q]);
             }
-        }
         // The next tile goes to the idle buffer before this tile's stores are
         // issued: the wait for its loads counts every earlier vector memory
         // operation, stores included, so stashing after the stores would
@@ -782,8 +804,8 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
         if (a.pair) {
             const bool odd = c & 1;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = 64 * ct + 16 * q + c;   // n and n ^ 1 lie on one side of ncols
+            for (int q = 0; q < NQ; ++q) {
+                const int n = L::CT * ct + 16 * q + c;   // n and n ^ 1 lie on one side of ncols
                 if (n >= a.ncols)
                     continue;
                 const float bias = colbias[n];
@@ -791,39 +813,42 @@ __global__ void __launch_bounds__(64 * kRkWaves) block_gemm_rk_kernel(BlockArgs 
                 const uint32_t col = coltab[it & 1][cp];
                 typename E::T *dst = static_cast<typename E::T *>(a.out0);
 #pragma unroll
-                for (int pp = 0; pp < 2; ++pp) {
-                    const float v0 = acc[q][2 * pp] + bias, v1 = acc[q][2 * pp + 1] + bias;
+                for (int rp = 0; rp < 2 * RT; ++rp) {
+                    const int rt = rp >> 1, pp = rp & 1;
+                    const float v0 = acc[rt][q][2 * pp] + bias, v1 = acc[rt][q][2 * pp + 1] + bias;
                     const float recv = dpp_xor1(odd ? v0 : v1);
                     const float lo = odd ? recv : v0, hi = odd ? v1 : recv;
-                    const int i = 2 * pp + (odd ? 1 : 0);
-                    if (rowok[i]) {
+                    const bool ok = odd ? rowok[rt][2 * pp + 1] : rowok[rt][2 * pp];
+                    const uint32_t ro = odd ? rowoff[rt][2 * pp + 1] : rowoff[rt][2 * pp];
+                    if (ok) {
                         if constexpr (BF)
-                            *reinterpret_cast<uint32_t *>(dst + (rowoff[i] + col)) =
+                            *reinterpret_cast<uint32_t *>(dst + (ro + col)) =
                                 cvt_bf16x2(lo, hi);   // RNE
                         else
-                            *reinterpret_cast<float2 *>(dst + (rowoff[i] + col)) =
-                                make_float2(lo, hi);
+                            *reinterpret_cast<float2 *>(dst + (ro + col)) = make_float2(lo, hi);
                     }
                 }
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = 64 * ct + 16 * q + c;
+            for (int q = 0; q < NQ; ++q) {
+                const int n = L::CT * ct + 16 * q + c;
                 if (n >= a.ncols)
                     continue;
                 const float bias = colbias[n];
                 const uint32_t col = coltab[it & 1][16 * q + c];
                 typename E::T *dst = static_cast<typename E::T *>(a.out0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (rowok[i]) {
-                        const float v = acc[q][i] + bias;
-                        if constexpr (BF)
-                            dst[rowoff[i] + col] = uint16_t(cvt_bf16x2(v, 0.f));   // RNE
-                        else
-                            dst[rowoff[i] + col] = v;
-                    }
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (rowok[rt][i]) {
+                            const float v = acc[rt][q][i] + bias;
+                            if constexpr (BF)
+                                dst[rowoff[rt][i] + col] = uint16_t(cvt_bf16x2(v, 0.f));   // RNE
+                            else
+                                dst[rowoff[rt][i] + col] = v;
+                        }
             }
         }
         __syncthreads();
@@ -834,7 +859,14 @@ template <class E, bool PROJ, int KP>
 void launch_rk(const BlockArgs &a, hipStream_t stream)
 {
     const unsigned blocks = unsigned((a.rows + kRkRows - 1) / kRkRows);
-    hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP>), dim3(blocks), dim3(64 * kRkWaves), 0,
+    if constexpr (!PROJ && E::bytes == 2) {
+        if (a.lnw) {
+            hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, true>), dim3(blocks),
+                               dim3(rk_threads<E>()), 0, stream, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP>), dim3(blocks), dim3(rk_threads<E>()), 0,
                        stream, a);
 }
 
@@ -846,7 +878,7 @@ bool try_rk(const BlockArgs &a, hipStream_t stream)
     if (a.rows * int64_t(a.C) >= (int64_t(1) << 31) ||
         int64_t(a.C) * a.ncols >= (int64_t(1) << 31))
         return false;   // 32-bit element offsets
-    if ((a.rows + kRkRows - 1) / kRkRows * 64 * kRkWaves >= (int64_t(1) << 32))
+    if ((a.rows + kRkRows - 1) / kRkRows * rk_threads<E>() >= (int64_t(1) << 32))
         return false;   // fewer than 2^32 work-items in the grid
     // A as 4-byte words: bf16 needs an even C, and in PROJ an even d_h (a word
     // never straddles two heads); the A base 4-byte aligned
@@ -919,7 +951,7 @@ static int rk_kp(int C)
 template <class E, int KP>
 size_t wpack_words(int ncols)
 {
-    return size_t((ncols + 63) / 64) * RkLds<E, KP>::tile;
+    return size_t((ncols + 63) / 64) * RkLds<E, KP>::image;
 }
 
 template <class E>
@@ -1004,6 +1036,9 @@ hipError_t launch_block_gemm(const BlockGemm &g, hipStream_t stream)
     a.out2 = g.out2;
     a.pair = false;
     a.ostride = 0;
+    a.lnw = g.lnw;
+    a.lnb = g.lnb;
+    a.eps = g.eps;
     if (g.dtype == 0)
         g.proj ? launch_gemm<F32, true>(a, stream) : launch_gemm<F32, false>(a, stream);
     else

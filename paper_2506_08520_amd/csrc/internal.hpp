@@ -65,6 +65,10 @@ struct BlockGemm {
     bool proj;
     const void *a, *wt, *bias, *wpk;
     void *out0, *out1, *out2;
+    // LayerNorm of A's rows before the product (bf16 QKV of a layer that
+    // layer_supported() accepts), or null
+    const void *lnw = nullptr, *lnb = nullptr;
+    float eps = 0.f;
 };
 bool block_gemm_supported(int64_t rows, int C);
 hipError_t launch_block_gemm(const BlockGemm &g, hipStream_t stream);
@@ -74,6 +78,20 @@ hipError_t launch_block_gemm(const BlockGemm &g, hipStream_t stream);
 size_t block_wpack_bytes(int C, int ncols, int dtype);
 hipError_t launch_block_wpack(const void *wqkv, const void *wproj, int C, int dtype, void *pk_qkv,
                               void *pk_proj, hipStream_t stream);
+
+// The rest of a transformer layer after the attention: x1 = X + O W_proj + b,
+// Y = x1 + W2 gelu(W1 LayerNorm(x1) + b1) + b2 (W1 [hidden][C], W2 [C][hidden]).
+// `gemm` is the block's PROJ product (out0 = Y).  layer_supported() tests what
+// this and the QKV product with LayerNorm need: bf16, C and hidden multiples
+// of 4, C <= 256, even heads, 32-bit offsets.
+struct LayerTail {
+    BlockGemm gemm;
+    const void *x, *lnw, *lnb, *w1, *b1, *w2, *b2;
+    float eps;
+    int hidden;
+};
+bool layer_supported(int64_t rows, int C, int heads, int dtype, int hidden);
+hipError_t launch_layer_tail(const LayerTail &t, hipStream_t stream);
 
 // Head widths with a tiled instantiation: the multiples of 4 from 8 to 32
 // (Dehazeformer's 12 and 16, Uformer's 32) and SwinIR's 30.

@@ -10,7 +10,9 @@ autograd history.
 
 ``SwinTransformerBlock`` is the transformer block those models stack
 (LayerNorm, window attention, residual, LayerNorm, MLP, residual), with the
-window attention replaced; LayerNorm and the MLP are plain torch layers.
+window attention replaced; LayerNorm and the MLP are plain torch layers, run
+as such or, where nothing observes or alters them, by the fused bf16 kernels of
+nystra_layer_forward with the same weights.
 Relative-position bias and the shifted-window mask are not applied: Eqs.
 (1)-(8) have neither.
 """
@@ -107,7 +109,70 @@ class SwinTransformerBlock(nn.Module):
         self.mlp = nn.Sequential(nn.Linear(dim, hidden, **kw), nn.GELU(),
                                  nn.Linear(hidden, dim, **kw))
 
+    def _fusable(self, x):
+        """Whether nystra_layer_forward computes what the composition of the
+        layers does: plain layers of their exact types with bf16 weights on x's
+        device, no hook on any of them, no autocast, tracing, compilation, transform,
+        forward-mode level or torch mode that would see the torch calls.
+
+        fp32, and more than 256 channels, keep the composition (there is no fused
+        kernel for them)."""
+        n1, n2, attn, mlp = self.norm1, self.norm2, self.attn, self.mlp
+        if (type(x) is not torch.Tensor or x.dtype != torch.bfloat16 or not x.is_cuda or
+                x.dim() != 4 or x.numel() == 0 or type(attn) is not NystraWindowAttention or
+                type(n1) is not nn.LayerNorm or type(n2) is not nn.LayerNorm or
+                type(mlp) is not nn.Sequential or len(mlp) != 3):
+            return False
+        fc1, act, fc2 = mlp
+        C = x.shape[-1]
+        if (type(fc1) is not nn.Linear or type(act) is not nn.GELU or type(fc2) is not nn.Linear or
+                act.approximate != "none" or attn.dim != C or C > 256 or C % 4 != 0 or
+                attn.heads < 1 or (C // attn.heads) % 2 != 0 or
+                n1.normalized_shape != (C,) or n2.normalized_shape != (C,)):
+            return False
+        hidden = fc1.weight.shape[0]
+        want = ((n1.weight, (C,)), (n1.bias, (C,)), (n2.weight, (C,)), (n2.bias, (C,)),
+                (fc1.weight, (hidden, C)), (fc2.weight, (C, hidden)), (fc1.bias, (hidden,)),
+                (fc2.bias, (C,)), (attn.w_qkv, (C, 3 * C)), (attn.b_qkv, (3 * C,)),
+                (attn.w_proj, (C, C)), (attn.b_proj, (C,)))
+        for t, shape in want:
+            if t is None and shape in ((hidden,), (C,)) and (t is fc1.bias or t is fc2.bias):
+                continue
+            if (type(t) not in (nn.Parameter, torch.Tensor) or t.dtype != x.dtype or
+                    t.device != x.device or tuple(t.shape) != shape or not t.is_contiguous()):
+                return False
+        if hidden % 4 != 0 or hidden < 4 or any(
+                t.data_ptr() % 4 != 0 for t in (x, fc1.weight, fc2.weight)):
+            return False
+        if any(p.data_ptr() % 4 != 0 for p in (attn.w_qkv, attn.w_proj)):
+            return False
+        if 3 * (x.numel() + 128) >= 1 << 32 or x.numel() >= 1 << 31:
+            return False
+        mod = nn.modules.module
+        if (mod._global_forward_hooks or mod._global_forward_pre_hooks or
+                any(s._forward_hooks or s._forward_pre_hooks or "forward" in s.__dict__
+                    for s in (n1, n2, attn, mlp, fc1, act, fc2))):
+            return False
+        return not (torch.is_autocast_enabled("cuda") or torch.jit.is_tracing() or
+                    torch.compiler.is_compiling() or torch._C._len_torch_function_stack() or
+                    torch._C._len_torch_dispatch_stack() or
+                    torch._C._functorch.peek_interpreter_stack() is not None or
+                    torch.autograd.forward_ad._current_level >= 0)
+
+    def _forward_fused(self, x):
+        attn, (fc1, _, fc2) = self.attn, self.mlp
+        x = x.contiguous()
+        ws, att = attn._workspace(x)
+        return B.nystra_layer_forward(
+            x, attn.w_qkv, attn.b_qkv, attn.w_proj, attn.b_proj, attn._packed_weights(),
+            (self.norm1.weight, self.norm1.bias, self.norm1.eps),
+            (self.norm2.weight, self.norm2.bias, self.norm2.eps), fc1.weight, fc1.bias,
+            fc2.weight, fc2.bias, attn.heads, attn.window, shift=attn.shift, m=attn.m,
+            opts=attn.opts, attention=att, workspace=ws)
+
     @torch.no_grad()
     def forward(self, x):
+        if self._fusable(x):
+            return self._forward_fused(x)
         x = x + self.attn(self.norm1(x))
         return x + self.mlp(self.norm2(x))

@@ -1,0 +1,161 @@
+"""The fused bf16 transformer layer against the composition of torch layers it
+stands for, both measured against float64: LayerNorm, block, residual,
+LayerNorm, MLP, residual.  The fused path keeps the residual stream and the
+MLP's sums in fp32 where the composition rounds them to bf16, so its error must
+not be larger than the composition's (with 10% for the other draw of
+roundings), besides a bound of its own."""
+import numpy as np
+import pytest
+import torch
+from scipy.special import erf
+from torch import nn
+
+from oracle import block as OB
+from paper_2506_08520_amd.module import SwinTransformerBlock
+
+pytestmark = pytest.mark.gpu
+
+
+def make(C, heads, w, s, m, attention, ratio=2.0, seed=0):
+    torch.manual_seed(seed)
+    blk = SwinTransformerBlock(C, heads, w, s, m=m, mlp_ratio=ratio, attention=attention,
+                               dtype=torch.bfloat16)
+    with torch.no_grad():
+        blk.attn.w_qkv.copy_(torch.randn(C, 3 * C) / C ** 0.5)
+        blk.attn.b_qkv.copy_(0.02 * torch.randn(3 * C))
+        blk.attn.w_proj.copy_(torch.randn(C, C) / C ** 0.5)
+        blk.attn.b_proj.copy_(0.02 * torch.randn(C))
+        for ln in (blk.norm1, blk.norm2):
+            ln.weight.copy_(1 + 0.1 * torch.randn(C))
+            ln.bias.copy_(0.1 * torch.randn(C))
+        blk.mlp[0].weight.mul_(1.7)
+        blk.mlp[2].weight.mul_(1.7)
+    return blk.eval()
+
+
+def composed(blk, x):
+    """The layer as separate torch layers around the attention module."""
+    x = x + blk.attn(blk.norm1(x))
+    return x + blk.mlp(blk.norm2(x))
+
+
+def n64(t):
+    return t.detach().double().cpu().numpy()
+
+
+def layer_norm(x, ln):
+    mu = x.mean(-1, keepdims=True)
+    var = ((x - mu) ** 2).mean(-1, keepdims=True)
+    return (x - mu) / np.sqrt(var + ln.eps) * n64(ln.weight) + n64(ln.bias)
+
+
+def exact(blk, x):
+    a, (l1, _, l2) = blk.attn, blk.mlp
+    xn = n64(x)
+    h = xn + OB.block_forward(layer_norm(xn, blk.norm1), n64(a.w_qkv), n64(a.b_qkv),
+                              n64(a.w_proj), n64(a.b_proj), heads=a.heads, window=a.window,
+                              shift=a.shift, m=max(a.m, 1), attention=a.attention)
+    b1 = 0 if l1.bias is None else n64(l1.bias)
+    b2 = 0 if l2.bias is None else n64(l2.bias)
+    u = layer_norm(h, blk.norm2) @ n64(l1.weight).T + b1
+    return h + (0.5 * u * (1 + erf(u / np.sqrt(2)))) @ n64(l2.weight).T + b2
+
+
+# Channels at and beside each padded width (32, 64, 128, 192, 256), rows that
+# leave a partial row tile (4 x 12 = 48, 15 x 20 = 300), hidden widths with a
+# partial last step (4, 36, 360), and both attentions.
+CASES = [
+    (1, 4, 12, 4, 2, 4, 2, 4, "nystrom", 1.0),
+    (1, 15, 20, 28, 1, 5, 2, 1, "nystrom", 9 / 7),
+    (2, 8, 16, 32, 1, 8, 4, 8, "nystrom", 2.0),
+    (1, 16, 24, 36, 1, 8, 0, 16, "exact", 1.0),
+    (1, 16, 16, 64, 2, 16, 8, 32, "nystrom", 4.0),
+    (1, 20, 30, 96, 6, 10, 5, 25, "nystrom", 2.0),
+    (1, 16, 16, 128, 4, 8, 4, 16, "nystrom", 2.0),
+    (2, 24, 16, 180, 6, 8, 4, 16, "nystrom", 2.0),
+    (1, 8, 8, 192, 6, 8, 0, 16, "exact", 0.0625),
+    (1, 7, 21, 240, 8, 7, 3, 7, "nystrom", 2.0),
+    (1, 16, 32, 256, 8, 8, 4, 16, "nystrom", 2.0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_fused_layer(case):
+    Bn, H, Wd, C, heads, w, s, m, attention, ratio = case
+    blk = make(C, heads, w, s, m, attention, ratio)
+    x = torch.randn(Bn, H, Wd, C, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    assert blk._fusable(x)
+    ref = exact(blk, x)
+    y, z = blk(x), composed(blk, x)
+    rms = np.sqrt((ref ** 2).mean())
+    e = {k: np.sqrt(((n64(t) - ref) ** 2).mean()) / rms for k, t in (("fused", y), ("composed", z))}
+    print(f"layer {case}: rel {e}")
+    # bf16 roundings of the normalised rows, Q/K/V, O, the hidden units and Y:
+    # about six of 2^-9 / sqrt(3) each, amplified by the pseudo-inverse.
+    assert e["fused"] <= 1.3e-2
+    assert e["fused"] <= 1.1 * e["composed"]
+    assert np.abs(n64(y) - ref).max() <= 0.15 * rms
+
+
+def test_no_biases():
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    blk.mlp[0].bias = blk.mlp[2].bias = None
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    assert blk._fusable(x)
+    ref = exact(blk, x)
+    assert np.sqrt(((n64(blk(x)) - ref) ** 2).mean() / (ref ** 2).mean()) <= 1.3e-2
+
+
+def test_weights_are_read_every_call():
+    """Writes through .data (no version bump) to the norms and the MLP count."""
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    blk(x)
+    for p in (blk.norm1.weight, blk.norm2.bias, blk.mlp[0].weight, blk.mlp[2].weight,
+              blk.mlp[2].bias):
+        p.data.mul_(1.5)
+    ref = exact(blk, x)
+    assert np.sqrt(((n64(blk(x)) - ref) ** 2).mean() / (ref ** 2).mean()) <= 1.3e-2
+
+
+def test_large_values_and_gelu_tails():
+    """Hidden units far into both tails of the GELU, rows with a large mean."""
+    blk = make(64, 2, 8, 0, 16, "exact", 4.0)
+    with torch.no_grad():
+        blk.mlp[0].weight.mul_(10)
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(9)) * 3 + 40
+    x = x.bfloat16().cuda()
+    ref, y, z = exact(blk, x), blk(x), composed(blk, x)
+    rms = np.sqrt((ref ** 2).mean())
+    assert np.sqrt(((n64(y) - ref) ** 2).mean()) <= 1.1 * np.sqrt(((n64(z) - ref) ** 2).mean())
+    assert np.isfinite(n64(y)).all() and rms > 0
+
+
+class _Twice(nn.Linear):
+    def forward(self, x):
+        return 2 * super().forward(x)
+
+
+def test_observed_or_altered_layers_are_composed():
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    seen = []
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    h = blk.mlp[1].register_forward_hook(lambda *a: seen.append(1))
+    assert not blk._fusable(x) and torch.equal(blk(x), composed(blk, x)) and seen
+    h.remove()
+    assert blk._fusable(x)
+    blk.mlp[1] = nn.GELU(approximate="tanh")
+    assert not blk._fusable(x)
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    lin = _Twice(64, 128, dtype=torch.bfloat16, device="cuda")
+    lin.load_state_dict(blk.mlp[0].state_dict())
+    blk.mlp[0] = lin
+    assert not blk._fusable(x) and torch.equal(blk(x), composed(blk, x))
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    assert not blk._fusable(x.float())
+    with torch.autocast("cuda", dtype=torch.bfloat16):
+        assert not blk._fusable(x)
+    with torch.autograd.forward_ad.dual_level():
+        assert not blk._fusable(x)
+    assert blk._fusable(x.transpose(1, 2))   # other strides: made contiguous
+    assert torch.equal(blk(x.transpose(1, 2)), blk(x.transpose(1, 2).contiguous()))
