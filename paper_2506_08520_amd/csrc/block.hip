@@ -422,21 +422,6 @@ bool wide_ok(const BlockArgs &a, bool proj)
     return a.C % 8 == 0 && a.dh % 8 == 0 && p % 4 == 0;
 }
 
-// Register-resident variant for C <= 256 (K padded to KP, a multiple of 32).
-// Each wave holds its RT row tiles of A for the whole contraction in
-// registers, in the operand layout of the matrix cores: lane group g takes the
-// contiguous quarter k in [g KP/4, (g+1) KP/4), so A is read from memory exactly
-// once.  The workgroup's waves (128 rows) stream W through LDS one tile of
-// CT columns at a time, double-buffered: the next tile's loads are in flight
-// while the current one is multiplied.  W tiles in LDS: transposed bf16, [n][k]
-// (eight k per 16-byte read); fp32 operands are carried as three bf16 terms
-// (mfma_split3), A split once into registers, W on the way into LDS, a tile
-// there holding the three planes one after another.
-// LDS reads bound the loop: a W operand read (8 cycles of the CU's LDS, 32 for
-// its four SIMDs) feeds RT matrix instructions of 16 cycles (96 in fp32), so two
-// row tiles a wave halve the LDS time of one.  CT is the widest tile that lets
-// two workgroups share a CU's 160 KB.
-// MEASURED_RK
 // Packs W [C][ncols], transposed, by 64-column tiles, one after another: [n][k]
 // with pitch PH halves (bf16, the tile's LDS image) or KP floats.  Every slot
 // outside W (k >= C, n >= ncols, the pitch padding) is zero.  The second matrix's
@@ -497,19 +482,127 @@ __global__ void __launch_bounds__(256) block_wpack_kernel(WPackArgs p)
     reinterpret_cast<u32x4 *>(second ? p.d1 : p.d0)[int64_t(ct) * kPieces + dst] = out;
 }
 
+// acc[q] = A (KS steps of 32 k, NP planes) times column tile q of a W tile in LDS;
+// h points at this lane's slot of the tile's first column, steps lie `step`
+// halves apart.
+template <class L, int KS>
+__device__ inline void tile_product(const bf8 (&ab)[L::NP][KS], const uint16_t *h, int step,
+                                    f4 (&acc)[L::CT / 16])
+{
+    constexpr int NQ = L::CT / 16;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (L::NP == 1) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                acc[q] = mfma_bf16(
+                    ab[0][s], *reinterpret_cast<const bf8 *>(&h[16 * q * L::PH + step * s]), acc[q]);
+    } else {
+        // The six products of mfma_split3, the small ones in accumulators of their
+        // own and the column tiles side by side: several chains of dependent
+        // instructions at a time.
+        f4 low[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            low[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            bf8 bv[NQ][3];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    bv[q][p] = *reinterpret_cast<const bf8 *>(
+                        &h[2 * p * L::plane + 16 * q * L::PH + step * s]);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                low[q] = mfma_bf16(ab[2][s], bv[q][0], low[q]);
+                acc[q] = mfma_bf16(ab[1][s], bv[q][0], acc[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                low[q] = mfma_bf16(ab[0][s], bv[q][2], low[q]);
+                acc[q] = mfma_bf16(ab[0][s], bv[q][1], acc[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                low[q] = mfma_bf16(ab[1][s], bv[q][1], low[q]);
+                acc[q] = mfma_bf16(ab[0][s], bv[q][0], acc[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            acc[q] += low[q];
+    }
+}
+
+// Stores a tile of CT columns from column n0 on: lane (g, c) holds rows 4g + i,
+// column c of each 16 x 16 tile; destination = row part (rowoff) + column part
+// (coltab).  With a.pair, lanes c and c ^ 1 swap one value per two rows so that
+// the even lane holds columns (c, c + 1) of row 4g + 2p and the odd lane those
+// of row 4g + 2p + 1: one 4-byte (bf16) or 8-byte (fp32) store per two outputs.
+// Pairs never straddle a head or Q/K/V (d_h and C even).
+template <class E, class L>
+__device__ inline void store_tile(const BlockArgs &a, const f4 (&acc)[L::CT / 16], int n0, int c,
+                                  const uint32_t (&rowoff)[4], const bool (&rowok)[4],
+                                  const float *bias, const uint32_t *coltab)
+{
+    constexpr bool BF = E::bytes == 2;
+    typename E::T *dst = static_cast<typename E::T *>(a.out0);
+    const bool odd = c & 1;
+#pragma unroll
+    for (int q = 0; q < L::CT / 16; ++q) {
+        const int j = 16 * q + c;
+        if (n0 + j >= a.ncols)   // column pairs lie on one side of ncols
+            continue;
+        const float b = bias[j];
+        if (a.pair) {
+            const uint32_t col = coltab[j & ~1];
+#pragma unroll
+            for (int pp = 0; pp < 2; ++pp) {
+                const float v0 = acc[q][2 * pp] + b, v1 = acc[q][2 * pp + 1] + b;
+                const float recv = dpp_xor1(odd ? v0 : v1);
+                const float lo = odd ? recv : v0, hi = odd ? v1 : recv;
+                const bool ok = odd ? rowok[2 * pp + 1] : rowok[2 * pp];
+                const uint32_t ro = odd ? rowoff[2 * pp + 1] : rowoff[2 * pp];
+                if (ok) {
+                    if constexpr (BF)
+                        *reinterpret_cast<uint32_t *>(dst + (ro + col)) = cvt_bf16x2(lo, hi);   // RNE
+                    else
+                        *reinterpret_cast<float2 *>(dst + (ro + col)) = make_float2(lo, hi);
+                }
+            }
+        } else {
+            const uint32_t col = coltab[j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (rowok[i]) {
+                    const float v = acc[q][i] + b;
+                    if constexpr (BF)
+                        dst[rowoff[i] + col] = uint16_t(cvt_bf16x2(v, 0.f));   // RNE
+                    else
+                        dst[rowoff[i] + col] = v;
+                }
+        }
+    }
+}
+
 // LN (bf16, QKV): the rows of A are normalised (LayerNorm over C, affine) once
 // they are in registers -- a row's quarters lie in the four lane groups, so its
 // sums take two cross-lane steps -- and rounded to bf16 as the norm's own output
 // would be: the map is neither written nor read in between.
 template <class E, bool PROJ, int KP, bool LN = false>
-__global__ void __launch_bounds__(rk_threads<E>()) 
+__global__ void __launch_bounds__(kRkThreads) 
 __attribute__((amdgpu_waves_per_eu(E::bytes == 4 || LN ? 2 : 4)))
 block_gemm_rk_kernel(BlockArgs a)
 {
     constexpr bool BF = E::bytes == 2;
     using L = RkLds<E, KP>;
     constexpr int KQ = KP / 4;               // contraction slots per lane group
-    constexpr int RT = rk_rt<E>(), NQ = L::CT / 16, kRkThreads = rk_threads<E>();
+    constexpr int NQ = L::CT / 16;
     __shared__ __align__(16) float lds_all[L::total];
     auto wbuf = [&](int b) { return lds_all + b * L::tile; };
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -519,7 +612,7 @@ block_gemm_rk_kernel(BlockArgs a)
     // ---- A: the workgroup's 128 rows are staged in LDS, SR at a time, with
     // coalesced 4-byte loads (lanes take consecutive words of a row; bf16 words
     // hold two elements), then each lane copies its operand slots -- rows
-    // 16 (RT wv + rt) + c, k = g KQ + s -- into registers.  The stage and its
+    // 16 wv + c, k = g KQ + s -- into registers.  The stage and its
     // offset tables share LDS with the W tiles.
     constexpr int EPW = BF ? 2 : 1;              // elements per 4-byte word
     constexpr int AWL = L::AWL, AP = L::AP;
@@ -612,7 +705,7 @@ block_gemm_rk_kernel(BlockArgs a)
         const int nc = n < a.ncols ? n : a.ncols - 1;
         bz[j] = a.bias ? ld<E>(a.bias, nc) : 0.f;
     }
-    bf8 ab[RT][L::NP][KQ / 8];
+    bf8 ab[L::NP][KQ / 8];
     const uint32_t *asrc = static_cast<const uint32_t *>(a.a);
     uint32_t *adst = reinterpret_cast<uint32_t *>(astage);
 #pragma unroll
@@ -644,38 +737,35 @@ block_gemm_rk_kernel(BlockArgs a)
             }
         }
         __syncthreads();
-        if (16 * RT * wv / L::SR == ph) {   // uniform: this wave's rows
+        if (16 * wv / L::SR == ph) {   // uniform: this wave's rows
+            const float *arow = astage + (16 * wv % L::SR + c) * AP;
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const float *arow = astage + (16 * RT * wv % L::SR + 16 * rt + c) * AP;
-#pragma unroll
-                for (int s = 0; s < KQ / 8; ++s) {
-                    if constexpr (BF) {
-                        ab[rt][0][s] = *reinterpret_cast<const bf8 *>(arow + (g * KQ + 8 * s) / 2);
-                    } else {
-                        const f4 lo = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s);
-                        const f4 hi = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s + 4);
-                        const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                        split3_bf16(x, ab[rt][0][s], ab[rt][L::NP / 2][s], ab[rt][L::NP - 1][s]);
-                    }
+            for (int s = 0; s < KQ / 8; ++s) {
+                if constexpr (BF) {
+                    ab[0][s] = *reinterpret_cast<const bf8 *>(arow + (g * KQ + 8 * s) / 2);
+                } else {
+                    const f4 lo = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s);
+                    const f4 hi = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s + 4);
+                    const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                    split3_bf16(x, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s]);
                 }
             }
         }
     }
     if constexpr (LN) {
-        static_assert(BF && RT == 1, "LayerNorm in the prologue: bf16");
+        static_assert(BF, "LayerNorm in the prologue: bf16");
         // The rows stay packed between the three passes over them: without
         // this the unpacked values of the first pass are kept, and spilled.
         auto keep_packed = [&]() {
 #pragma unroll
             for (int s = 0; s < KQ / 8; ++s)
-                asm volatile("" : "+v"(ab[0][0][s]));
+                asm volatile("" : "+v"(ab[0][s]));
         };
         float sum = 0.f, sq = 0.f;
 #pragma unroll
         for (int s = 0; s < KQ / 8; ++s) {
             float f[8];
-            unpack_bf8(ab[0][0][s], f);
+            unpack_bf8(ab[0][s], f);
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 sum += f[e];   // zero from k = C on
@@ -685,7 +775,7 @@ block_gemm_rk_kernel(BlockArgs a)
 #pragma unroll
         for (int s = 0; s < KQ / 8; ++s) {
             float f[8];
-            unpack_bf8(ab[0][0][s], f);
+            unpack_bf8(ab[0][s], f);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float d = g * KQ + 8 * s + e < a.C ? f[e] - mean : 0.f;
@@ -697,14 +787,14 @@ block_gemm_rk_kernel(BlockArgs a)
 #pragma unroll
         for (int s = 0; s < KQ / 8; ++s) {
             float f[8];
-            unpack_bf8(ab[0][0][s], f);
+            unpack_bf8(ab[0][s], f);
             const float *lw = lnt + g * KQ + 8 * s, *lb = lw + KP;
             U16B u;
 #pragma unroll
             for (int p = 0; p < 4; ++p)   // weight and bias are zero from C on
                 u.w[p] = cvt_bf16x2(fmaf((f[2 * p] - mean) * rstd, lw[2 * p], lb[2 * p]),
                                     fmaf((f[2 * p + 1] - mean) * rstd, lw[2 * p + 1], lb[2 * p + 1]));
-            ab[0][0][s] = __builtin_bit_cast(bf8, u);
+            ab[0][s] = __builtin_bit_cast(bf8, u);
             __builtin_amdgcn_sched_barrier(0);   // few table reads in flight: registers
         }
     }
@@ -732,19 +822,17 @@ block_gemm_rk_kernel(BlockArgs a)
     // (window wn, token tt) -> wn N C + tt d_h; PROJ -> pixel C.  Offsets are
     // unsigned 32-bit (tensors under 2^31 elements); rows past the end are
     // not stored.
-    uint32_t rowoff[RT][4];
-    bool rowok[RT][4];
+    uint32_t rowoff[4];
+    bool rowok[4];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = int(m0) + 16 * (RT * wv + rt) + 4 * g + i;   // rows < 2^31
-            rowok[rt][i] = row < a.rows;
-            const int rr = rowok[rt][i] ? row : 0;
-            const int wn = rr / a.N, tt = rr - wn * a.N;
-            rowoff[rt][i] = uint32_t(PROJ ? pixel_of(a, wn, tt) * a.C
-                                          : int64_t(wn) * a.N * a.C + int64_t(tt) * a.dh);
-        }
+    for (int i = 0; i < 4; ++i) {
+        const int row = int(m0) + 16 * wv + 4 * g + i;   // rows < 2^31
+        rowok[i] = row < a.rows;
+        const int rr = rowok[i] ? row : 0;
+        const int wn = rr / a.N, tt = rr - wn * a.N;
+        rowoff[i] = uint32_t(PROJ ? pixel_of(a, wn, tt) * a.C
+                                  : int64_t(wn) * a.N * a.C + int64_t(tt) * a.dh);
+    }
 
 #pragma unroll
     for (int j = 0; j < kBiasPer; ++j) {
@@ -761,32 +849,9 @@ block_gemm_rk_kernel(BlockArgs a)
         if (more)
             wfetch(phys(it + 1));
         const float *wt = wbuf(it & 1);
-        f4 acc[RT][NQ];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                acc[rt][q] = f4{0.f, 0.f, 0.f, 0.f};
+        f4 acc[NQ];
         const uint16_t *h = reinterpret_cast<const uint16_t *>(wt);
-#pragma unroll
-        for (int s = 0; s < KQ / 8; ++s)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                bf8 bv[L::NP];
-#pragma unroll
-                for (int p = 0; p < L::NP; ++p)
-                    bv[p] = *reinterpret_cast<const bf8 *>(
-                        &h[2 * p * L::plane + (16 * q + c) * L::PH + g * KQ + 8 * s]);
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    if constexpr (BF)
-                        acc[rt][q] = mfma_bf16(ab[rt][0][s], bv[0], acc[rt][q]);
-                    else
-                        acc[rt][q] = mfma_split3(ab[rt][0][s], ab[rt][L::NP / 2][s],
-                                                 ab[rt][L::NP - 1][s], bv[0], bv[L::NP / 2],
-                                                 bv[L::NP - 1], acc[rt][q]);
-                }
-            }
+        tile_product<L, KQ / 8>(ab, h + c * L::PH + g * KQ, 8, acc);
         // The next tile goes to the idle buffer before this tile's stores are
         // issued: the wait for its loads counts every earlier vector memory
         // operation, stores included, so stashing after the stores would
@@ -801,73 +866,353 @@ block_gemm_rk_kernel(BlockArgs a)
         // even lane holds columns (c, c + 1) of row 4g + 2p and the odd lane
         // those of row 4g + 2p + 1: one 4-byte (bf16) or 8-byte (fp32) store per
         // two outputs.  Pairs never straddle a head or Q/K/V (d_h and C even).
-        if (a.pair) {
-            const bool odd = c & 1;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int n = L::CT * ct + 16 * q + c;   // n and n ^ 1 lie on one side of ncols
-                if (n >= a.ncols)
-                    continue;
-                const float bias = colbias[n];
-                const int cp = (16 * q + c) & ~1;
-                const uint32_t col = coltab[it & 1][cp];
-                typename E::T *dst = static_cast<typename E::T *>(a.out0);
-#pragma unroll
-                for (int rp = 0; rp < 2 * RT; ++rp) {
-                    const int rt = rp >> 1, pp = rp & 1;
-                    const float v0 = acc[rt][q][2 * pp] + bias, v1 = acc[rt][q][2 * pp + 1] + bias;
-                    const float recv = dpp_xor1(odd ? v0 : v1);
-                    const float lo = odd ? recv : v0, hi = odd ? v1 : recv;
-                    const bool ok = odd ? rowok[rt][2 * pp + 1] : rowok[rt][2 * pp];
-                    const uint32_t ro = odd ? rowoff[rt][2 * pp + 1] : rowoff[rt][2 * pp];
-                    if (ok) {
-                        if constexpr (BF)
-                            *reinterpret_cast<uint32_t *>(dst + (ro + col)) =
-                                cvt_bf16x2(lo, hi);   // RNE
-                        else
-                            *reinterpret_cast<float2 *>(dst + (ro + col)) = make_float2(lo, hi);
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int n = L::CT * ct + 16 * q + c;
-                if (n >= a.ncols)
-                    continue;
-                const float bias = colbias[n];
-                const uint32_t col = coltab[it & 1][16 * q + c];
-                typename E::T *dst = static_cast<typename E::T *>(a.out0);
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (rowok[rt][i]) {
-                            const float v = acc[rt][q][i] + bias;
-                            if constexpr (BF)
-                                dst[rowoff[rt][i] + col] = uint16_t(cvt_bf16x2(v, 0.f));   // RNE
-                            else
-                                dst[rowoff[rt][i] + col] = v;
-                        }
-            }
-        }
+        store_tile<E, L>(a, acc, L::CT * ct, c, rowoff, rowok, colbias + L::CT * ct, coltab[it & 1]);
         __syncthreads();
     }
 }
 
-template <class E, bool PROJ, int KP>
-void launch_rk(const BlockArgs &a, hipStream_t stream)
+// Weight-resident GEMM for C <= 256: a workgroup keeps a group of columns of W in
+// LDS for its whole life, and its eight waves walk over row tiles of 16 on their
+// own -- rows straight from memory into the operand registers (lane (g, c): row
+// c, k = 32 s + 8 g ..), the next tile's rows in flight while this one is
+// multiplied, no barrier after W has arrived.  Streaming W past resident rows
+// instead (64 columns at a time, one barrier each) chained every step to the
+// stores of the one before: memory operations complete in order, so the wait for
+// the next W tile waited for them too.
+// fp32: A is split into three bf16 terms in registers, W on its way into LDS.
+// LN (bf16, QKV): the rows are normalised (LayerNorm over C, affine) in registers
+// -- a row lies in the four lane groups, so its sums take two cross-lane steps --
+// and rounded to bf16 as the norm's own output would be: the map is neither
+// written nor read in between.
+// launch_rk_ln() says where this measured faster.
+template <class E, bool PROJ, int KP, bool LN = false>
+__global__ void __launch_bounds__(kRwThreads)
+__attribute__((amdgpu_waves_per_eu(E::bytes == 2 && !LN ? 4 : 2)))
+block_gemm_rw_kernel(BlockArgs a)
 {
-    const unsigned blocks = unsigned((a.rows + kRkRows - 1) / kRkRows);
+    constexpr bool BF = E::bytes == 2;
+    using L = RwLds<E, KP>;
+    constexpr int KS = KP / 32, T = kRwThreads, NQ = L::CT / 16;
+    typedef typename E::T ET;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) float lds_all[];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int *colofs = reinterpret_cast<int *>(lds_all);            // element k's offset in a row of A
+    float *lnt = lds_all + KP;                                 // LN: weight, bias (zero from C on)
+    float *colbias = lnt + (LN ? 2 * KP : 0);
+    uint32_t *coltab = reinterpret_cast<uint32_t *>(colbias + a.ctiles * L::CT);
+    float *wbase = reinterpret_cast<float *>(coltab + a.ctiles * L::CT);
+
+    // Block -> (row block, column group): the groups of one row block run on one
+    // XCD and share its L2 for the rows.
+    const int total = int(gridDim.x), q8 = total / 8, r8 = total % 8;
+    const int xcd = int(blockIdx.x) % 8, local = int(blockIdx.x) / 8;
+    const int lb = (xcd < r8 ? xcd * (q8 + 1) : r8 * (q8 + 1) + (xcd - r8) * q8) + local;
+    const int rb = lb / a.groups, grp = lb - rb * a.groups, rblocks = total / a.groups;
+    const int t0 = grp * a.ctiles;                             // first CT-column tile
+    const int nt = min(a.ctiles, (a.ncols + L::CT - 1) / L::CT - t0);
+
+    // ---- rows
+    const int ntiles = int((a.rows + 15) / 16), stride = rblocks * (T / 64);
+    uint32_t inoff = 0, outoff = 0;   // of lane's row c, tile rt + g stride
+    auto rows4 = [&](int rt) {
+        const int64_t r64 = int64_t(rt + int64_t(g) * stride) * 16 + c;
+        const uint32_t row = uint32_t(r64 < a.rows ? r64 : a.rows - 1);
+        const uint32_t wn = row / uint32_t(a.N), tt = row - wn * uint32_t(a.N);
+        const uint32_t per = uint32_t(a.nwy) * uint32_t(a.nwx);
+        const uint32_t b = wn / per, wi = wn - b * per;
+        const uint32_t wy = wi / uint32_t(a.nwx), wx = wi - wy * uint32_t(a.nwx);
+        const uint32_t ty = tt / uint32_t(a.w), tx = tt - ty * uint32_t(a.w);
+        uint32_t y = wy * a.w + ty + a.shift, x = wx * a.w + tx + a.shift;
+        y -= y >= uint32_t(a.H) ? a.H : 0;
+        x -= x >= uint32_t(a.W) ? a.W : 0;
+        const uint32_t pix = ((b * a.H + y) * a.W + x) * uint32_t(a.C);
+        inoff = PROJ ? (wn * a.heads * a.N + tt) * uint32_t(a.dh) : pix;
+        outoff = PROJ ? pix : wn * uint32_t(a.N) * uint32_t(a.C) + tt * uint32_t(a.dh);
+    };
+    const ET *asrc = static_cast<const ET *>(a.a);
+    constexpr int RW = BF ? 4 : 8;    // words per step
+    uint32_t raw[KS][RW], rawn[KS][RW];
+    // Rows as words: whole 16-byte pieces where the eight k of a step are adjacent
+    // (QKV; PROJ with d_h a multiple of 8), pairs (or single fp32 elements) of
+    // known offsets otherwise; slots from C on are zeroed when they are used.
+    const bool vec8 = !PROJ || a.dh % 8 == 0, pairs = BF || (a.C % 2 == 0 && (!PROJ || a.dh % 2 == 0));
+    auto fetch = [&](uint32_t base, uint32_t (&x)[KS][RW]) {
+        const ET *p = asrc + base;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k0 = 32 * s + 8 * g;
+            if (vec8 && (s < L::full || 32 * s + 32 <= a.C)) {   // uniform
+                const ET *q = p + (PROJ ? colofs[k0] : k0);
+#pragma unroll
+                for (int h = 0; h < RW / 4; ++h) {
+                    const U16B v = *reinterpret_cast<const U16B *>(q + 4 * h);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        x[s][4 * h + w] = v.w[w];
+                }
+            } else if (pairs) {   // uniform
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int o = max(PROJ ? colofs[k0 + 2 * w] : (k0 + 2 * w < a.C ? k0 + 2 * w : 0), 0);
+                    if constexpr (BF) {
+                        x[s][w] = *reinterpret_cast<const uint32_t *>(p + o);
+                    } else {
+                        struct __attribute__((aligned(4))) P2 { uint32_t w[2]; };
+                        const P2 v = *reinterpret_cast<const P2 *>(p + o);
+                        x[s][2 * w] = v.w[0];
+                        x[s][2 * w + 1] = v.w[1];
+                    }
+                }
+            } else if constexpr (!BF) {
+#pragma unroll
+                for (int w = 0; w < 8; ++w)
+                    x[s][w] = __float_as_uint(p[max(colofs[k0 + w], 0)]);
+            }
+        }
+    };
+
+    // ---- prologue: W's pieces and the first rows are requested together, so
+    // that one memory latency covers them, then W goes to LDS.
+    // bf16: the packed image is the LDS image.  fp32: eight k of a column at a
+    // time (two pieces), split, one 16-byte piece per plane.
+    constexpr int WPP = BF ? 1 : 2, kUnit = BF ? L::tile / 4 : L::CT * KP / 8;
+    constexpr int kPer = (L::NT * kUnit + T - 1) / T;
+    const int units = nt * kUnit;
+    const u32x4 *wsrc = static_cast<const u32x4 *>(a.wpk);
+    constexpr int kBatch = kPer * WPP <= 12 ? kPer : 12 / WPP;   // pieces in flight
+    u32x4 wx[kBatch][WPP];
+    auto wfetch = [&](int j0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = min(j0 + tid + u * T, units - 1);
+            if constexpr (BF) {
+                wx[u][0] = wsrc[int64_t(t0) * kUnit + j];
+            } else {
+                const int col = t0 * L::CT + j / (KP / 8), kp = j % (KP / 8);
+                const u32x4 *src = wsrc + int64_t(col / 64) * (RkLds<E, KP>::image / 4) +
+                                   ((col % 64) * KP + 8 * kp) / 4;
+#pragma unroll
+                for (int h = 0; h < WPP; ++h)
+                    wx[u][h] = src[h];
+            }
+        }
+    };
+    auto wstash = [&](int j0) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = j0 + tid + u * T;
+            if (j < units) {
+                if constexpr (BF) {
+                    reinterpret_cast<u32x4 *>(wbase)[j] = wx[u][0];
+                } else {
+                    float f[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        f[e] = __uint_as_float(wx[u][e / 4 % WPP][e % 4]);
+                    const int cj = j / (KP / 8), kp = j % (KP / 8);
+                    bf8 *d = reinterpret_cast<bf8 *>(wbase + (cj / L::CT) * L::tile) +
+                             (cj % L::CT) * (L::PH / 8) + kp;
+                    split3_bf16(f, d[0], d[L::plane / 4], d[2 * (L::plane / 4)]);
+                }
+            }
+        }
+    };
+    wfetch(0);
+    for (int k = tid; k < KP; k += T) {
+        int off = k;
+        if constexpr (PROJ) {
+            const int hh = k / a.dh;
+            off = hh * a.N * a.dh + (k - hh * a.dh);
+        }
+        colofs[k] = k < a.C ? off : -1;
+        if constexpr (LN) {
+            lnt[k] = k < a.C ? ld<E>(a.lnw, k) : 0.f;
+            lnt[KP + k] = k < a.C ? ld<E>(a.lnb, k) : 0.f;
+        }
+    }
+    // Column part of the destination, from out0: (QKV) output tensor `which` at
+    // which * ostride, head h, feature f -> h N d_h + f; (PROJ) the column.
+    for (int j = tid; j < nt * L::CT; j += T) {
+        const int n = t0 * L::CT + j;
+        int which = 0, col = n;
+        if constexpr (!PROJ) {
+            which = n / a.C;
+            const int cc = n - which * a.C;
+            const int hh = cc / a.dh;
+            col = hh * a.N * a.dh + (cc - hh * a.dh);
+        }
+        coltab[j] = uint32_t(which * a.ostride + col);
+        colbias[j] = a.bias && n < a.ncols ? ld<E>(a.bias, n) : 0.f;
+    }
+    int rt = rb * (T / 64) + wv;
+    rows4(rt);   // clamped past the last row
+    int sub = 0;   // which of the four tiles of rows4 is current
+    if (PROJ || !pairs)
+        __syncthreads();   // colofs
+    fetch(__shfl(inoff, c, 64), raw);
+    wstash(0);
+    for (int j0 = kBatch * T; j0 < units; j0 += kBatch * T) {
+        wfetch(j0);
+        wstash(j0);
+    }
+    __syncthreads();
+    for (; rt < ntiles; rt += stride) {
+        // output offsets of rows 4g + i, then the next tile's rows
+        uint32_t rowoff[4];
+        bool rowok[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            rowoff[i] = __shfl(outoff, 16 * sub + 4 * g + i, 64);
+            rowok[i] = int64_t(rt) * 16 + 4 * g + i < a.rows;
+        }
+        // operands of this tile, zero from C on
+        bf8 ab[L::NP][KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int k0 = 32 * s + 8 * g;
+            if (s >= L::full && 32 * s + 32 > a.C) {   // uniform
+                constexpr int EW = BF ? 2 : 1;   // elements per word
+#pragma unroll
+                for (int w = 0; w < RW; ++w)
+                    raw[s][w] = k0 + EW * w < a.C ? raw[s][w] : 0u;
+            }
+            if constexpr (BF) {
+                const U16B u = {{raw[s][0], raw[s][1], raw[s][2], raw[s][3]}};
+                ab[0][s] = __builtin_bit_cast(bf8, u);
+            } else {
+                float f[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    f[e] = __uint_as_float(raw[s][e]);
+                split3_bf16(f, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s]);
+            }
+        }
+        if (++sub == 4) {   // uniform
+            sub = 0;
+            rows4(rt + stride);
+        }
+        if (rt + stride < ntiles)   // uniform
+            fetch(__shfl(inoff, 16 * sub + c, 64), rawn);
+        if constexpr (LN) {
+            static_assert(BF, "LayerNorm in the prologue: bf16");
+            // The rows stay packed between the three passes over them: without
+            // this the unpacked values of the first pass are kept, and spilled.
+            auto keep_packed = [&]() {
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    asm volatile("" : "+v"(ab[0][s]));
+            };
+            float sum = 0.f, sq = 0.f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                float f[8];
+                unpack_bf8(ab[0][s], f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    sum += f[e];
+            }
+            const float mean = sum_groups(sum) / float(a.C);
+            keep_packed();
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                float f[8];
+                unpack_bf8(ab[0][s], f);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float d = f[e] - mean;
+                    sq = fmaf(d, s < L::full || 32 * s + 8 * g + e < a.C ? d : 0.f, sq);
+                }
+            }
+            const float rstd = 1.f / sqrtf(sum_groups(sq) / float(a.C) + a.eps);
+            keep_packed();
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                float f[8];
+                unpack_bf8(ab[0][s], f);
+                const float *lw = lnt + 32 * s + 8 * g, *lb = lw + KP;
+                U16B u;
+#pragma unroll
+                for (int p = 0; p < 4; ++p)   // weight and bias are zero from C on
+                    u.w[p] = cvt_bf16x2(
+                        fmaf((f[2 * p] - mean) * rstd, lw[2 * p], lb[2 * p]),
+                        fmaf((f[2 * p + 1] - mean) * rstd, lw[2 * p + 1], lb[2 * p + 1]));
+                ab[0][s] = __builtin_bit_cast(bf8, u);
+                __builtin_amdgcn_sched_barrier(0);   // few table reads in flight: registers
+            }
+        }
+        for (int ct = 0; ct < nt; ++ct) {
+            const uint16_t *h = reinterpret_cast<const uint16_t *>(wbase + ct * L::tile);
+            f4 acc[NQ];
+            tile_product<L, KS>(ab, h + c * L::PH + 8 * g, 32, acc);
+            store_tile<E, L>(a, acc, (t0 + ct) * L::CT, c, rowoff, rowok, colbias + ct * L::CT,
+                             coltab + ct * L::CT);
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int w = 0; w < RW; ++w)
+                raw[s][w] = rawn[s][w];
+    }
+}
+
+// Column groups and row blocks: groups as wide as LDS allows (fewer passes over
+// the rows), narrower ones while that leaves compute units without a block, and
+// as many row blocks as fit on the chip at once.
+template <class E, bool PROJ, int KP, bool LN>
+void launch_rw_ln(BlockArgs &a, hipStream_t stream)
+{
+    using L = RwLds<E, KP>;
+    const int nct = (a.ncols + L::CT - 1) / L::CT;
+    const int64_t want = (a.rows + 127) / 128;       // blocks of eight row tiles
+    int per = L::NT;
+    while (per > 1 && want * ((nct + per - 1) / per) < 256)
+        per = (per + 1) / 2;
+    a.groups = (nct + per - 1) / per;
+    a.ctiles = (nct + a.groups - 1) / a.groups;
+    a.groups = (nct + a.ctiles - 1) / a.ctiles;
+    const size_t lds = 4 * (size_t(KP) * (LN ? 3 : 1) + size_t(a.ctiles) * (2 * L::CT + L::tile));
+    const int64_t fit = 256 * (lds * 2 <= 160 * 1024 ? 2 : 1);
+    int64_t rblocks = fit / a.groups;
+    if (rblocks < 1)
+        rblocks = 1;
+    if (rblocks > want)
+        rblocks = want;
+    hipLaunchKernelGGL((block_gemm_rw_kernel<E, PROJ, KP, LN>), dim3(unsigned(rblocks * a.groups)),
+                       dim3(kRwThreads), lds, stream, a);
+}
+
+template <class E, bool PROJ, int KP, bool LN>
+void launch_rk_ln(BlockArgs &a, hipStream_t stream)
+{
+    const int64_t blocks = (a.rows + kRkRows - 1) / kRkRows;
+    // Few rows (fewer row blocks than half the compute units): column groups on
+    // more of the chip.  4096 rows, whole blocks: C = 180 fp32 74 -> 39 us, C = 192
+    // bf16 37 -> 28 us, C = 240 bf16 47 -> 27 us.  With more rows every group's
+    // pass over them costs more than the streaming's waits: 25600 rows, C = 180
+    // bf16 47 us against 48, 65536 rows, C = 240 bf16 104 against 117, C = 96 fp32
+    // 88 against 131.  fp32 from 129 to 192 channels is the exception at any size
+    // (82944 rows, C = 180: 290 -> 257 us): 128 columns a group fit there, and the
+    // row-resident kernel has one workgroup's registers per CU to hide latency.
+    if (blocks < 128 || (E::bytes == 4 && KP == 192)) {
+        launch_rw_ln<E, PROJ, KP, LN>(a, stream);
+        return;
+    }
+    hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, LN>), dim3(unsigned(blocks)),
+                       dim3(kRkThreads), 0, stream, a);
+}
+
+template <class E, bool PROJ, int KP>
+void launch_rk(BlockArgs &a, hipStream_t stream)
+{
     if constexpr (!PROJ && E::bytes == 2) {
         if (a.lnw) {
-            hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, true>), dim3(blocks),
-                               dim3(rk_threads<E>()), 0, stream, a);
+            launch_rk_ln<E, PROJ, KP, true>(a, stream);
             return;
         }
     }
-    hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP>), dim3(blocks), dim3(rk_threads<E>()), 0,
-                       stream, a);
+    launch_rk_ln<E, PROJ, KP, false>(a, stream);
 }
 
 template <class E, bool PROJ>
@@ -878,7 +1223,7 @@ bool try_rk(const BlockArgs &a, hipStream_t stream)
     if (a.rows * int64_t(a.C) >= (int64_t(1) << 31) ||
         int64_t(a.C) * a.ncols >= (int64_t(1) << 31))
         return false;   // 32-bit element offsets
-    if ((a.rows + kRkRows - 1) / kRkRows * rk_threads<E>() >= (int64_t(1) << 32))
+    if ((a.rows + kRkRows - 1) / kRkRows * kRkThreads >= (int64_t(1) << 32))
         return false;   // fewer than 2^32 work-items in the grid
     // A as 4-byte words: bf16 needs an even C, and in PROJ an even d_h (a word
     // never straddles two heads); the A base 4-byte aligned

@@ -66,7 +66,7 @@ layer_tail_kernel(TailArgs a)
     using L = TailLds<KP>;
     using R = RkLds<BF16, KP>;
     constexpr int KQ = KP / 4, NT = KP / 16, AWL = R::AWL, AP = R::AP, T = 512;
-    static_assert(rk_threads<BF16>() == T && kRkRows == 128, "one row tile per wave");
+    static_assert(kRkThreads == T && kRkRows == 128, "one row tile per wave");
     __shared__ __align__(16) float lds[L::total];
     float *tbp = lds + L::tabs, *tlw = tbp + KP, *tlb = tlw + KP, *tb2 = tlb + KP;
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
