@@ -440,8 +440,9 @@ exact_blocked_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict_
     }
 }
 
-// ---- fp32, N a multiple of 64: the same blocked structure on the fp32 matrix
-// cores.  K rows and V^T are staged as fp32; S^T tiles are eight-step
+// ---- fp32, N = 64, 128 or 192: the same blocked structure on the fp32 matrix
+// cores (splitting a key block into bf16 terms, as below, costs more than the few
+// queries that share it gain: N = 64, 6144 units 46 us here, 67 us split).  K rows and V^T are staged as fp32; S^T tiles are eight-step
 // 16x16x4 products over the feature slots (the slot layout of load_chunk8);
 // the probabilities stay fp32 and feed O^T += V^T P^T directly in the
 // D-layout, with V^T read as the transposed left operand.
@@ -600,6 +601,276 @@ exact_blocked_f32_kernel(const float *__restrict__ q, const float *__restrict__ 
     }
 }
 
+// ---- fp32, N a multiple of 64 from 256 on: the same blocked structure ------------------
+//
+// Every product runs on the bf16 matrix cores with both operands as three bf16
+// terms (six products, mfma_split3): 96 cycles per 16x16x32 tile against 256 on
+// the fp32 matrix cores, which bounded the kernel before.  K, V and Q are split
+// once per workgroup, on their way into LDS (V transposed, its keys in the order
+// in which a lane group holds the probabilities) and registers; a probability is
+// split where it is used, and stays fp32 for the row sums.  What is left is
+// about even between the matrix instructions and the vector arithmetic of the
+// exponentials and their split.
+// Splitting an infinity would make NaN of its products with the (often zero)
+// lower terms of the other operand, so a block of keys that holds a value that is
+// not finite -- the staging threads flag it -- and every block of a query tile
+// group that does, takes the fp32 matrix cores.
+// 6144 units of 256 tokens, d_h = 30: 453 -> 361 us; error against 64 bits 3.2e-7 ->
+// 2.5e-7.  Two query tiles per wave (four waves per SIMD instead of two) measured
+// the same where they fit the registers (d_h = 16: 284 us against 287).
+
+struct SBufs {
+    static constexpr int kplane = kXB * kXKP;    // halves: K rows
+    static constexpr int vplane = 32 * kXVP;     // halves: V^T rows
+    static constexpr int flag = 3 * (kplane + vplane) * 2;   // bytes
+    static constexpr int bytes = flag + 16;
+};
+
+// Three-term split of finite non-negative values (probabilities).
+__device__ inline void split3_prob(const f4 &a, const f4 &b, bf8 &h, bf8 &m, bf8 &l)
+{
+    const NegSel s = neg_selectors();
+    U16B hw, mw, lw;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const float x0 = p < 2 ? a[2 * p] : b[2 * p - 4], x1 = p < 2 ? a[2 * p + 1] : b[2 * p - 3];
+        const float r0 = x0 - __uint_as_float(__float_as_uint(x0) & 0xffff0000u);
+        const float r1 = x1 - __uint_as_float(__float_as_uint(x1) & 0xffff0000u);
+        hw.w[p] = __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+        mw.w[p] = cvt_bf16x2(r0, r1);
+        lw.w[p] = residual_bf16x2(mw.w[p], r0, r1, s);
+    }
+    h = as_bf8(hw);
+    m = as_bf8(mw);
+    l = as_bf8(lw);
+}
+
+__device__ inline bool all_finite(const float (&x)[8])
+{
+    float m = 0.f;   // x - x is 0 for finite values, NaN otherwise
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        m += x[e] - x[e];
+    return m == 0.f;
+}
+
+template <int D, int QT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict__ k,
+                         const float *__restrict__ v, float *__restrict__ o, int N, float s2,
+                         int wpu)
+{
+    constexpr int NCT = (D + 15) / 16;
+    using X = SBufs;
+    extern __shared__ __attribute__((aligned(16))) unsigned char xsm[];
+    const int nw = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 4, c = lane & 15;
+    const int64_t unit = blockIdx.x / wpu;
+    const int wg = int(blockIdx.x - unit * wpu);
+    const int64_t base = unit * int64_t(N) * D;
+    const float *qu = q + base, *ku = k + base, *vu = v + base;
+    float *ou = o + base;
+    const int q0 = (wg * nw + w) * 16 * QT;
+
+    if constexpr (16 * NCT > D) {   // V^T rows past D are zero in both buffers
+        constexpr int kPad = (16 * NCT - D) * kXB;
+        for (int idx = threadIdx.x; idx < 6 * kPad; idx += blockDim.x) {
+            const int bp = idx / kPad, r = idx % kPad;   // buffer and plane
+            uint16_t *vt = reinterpret_cast<uint16_t *>(xsm + (bp / 3) * X::bytes) + 3 * X::kplane +
+                           (bp % 3) * X::vplane;
+            vt[(D + r / kXB) * kXVP + r % kXB] = uint16_t(0);
+        }
+    }
+    if (threadIdx.x < 2)
+        *reinterpret_cast<int *>(xsm + threadIdx.x * X::bytes + X::flag) = -1;
+    __syncthreads();
+    // Staging: thread t of the first 256 takes key t / 4, chunk t % 4.
+    const bool stager = threadIdx.x < 256;
+    const int skey = (threadIdx.x >> 2) & 63, sg = threadIdx.x & 3;
+    // key 4g + j (16 + 4g + j) of each 32 -> slot 8g + j (8g + 4 + j)
+    const int sslot = (skey & 35) + ((skey & 12) << 1) + ((skey & 16) >> 2);
+    float kst[8], vst[8];
+    auto fetch = [&](int blk) {
+        if (stager) {
+            const int64_t row = int64_t(blk * kXB + skey) * D + chunk_start<D>(sg);
+            load_row8<D>(ku + row, kst);
+            load_row8<D>(vu + row, vst);
+        }
+    };
+    auto store = [&](int buf, int blk) {
+        if (stager) {
+            unsigned char *bb = xsm + buf * X::bytes;
+            uint16_t *ks = reinterpret_cast<uint16_t *>(bb) + skey * kXKP + 8 * sg;
+            uint16_t *vt = reinterpret_cast<uint16_t *>(bb) + 3 * X::kplane;
+            // a buffer's flag names the last block in it with such a value
+            if (!all_finite(kst) || !all_finite(vst))
+                *reinterpret_cast<int *>(bb + X::flag) = blk;
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                kst[x] = slot_valid<D>(sg, x) ? kst[x] : 0.f;
+            split3_bf16(kst, *reinterpret_cast<bf8 *>(ks), *reinterpret_cast<bf8 *>(ks + X::kplane),
+                        *reinterpret_cast<bf8 *>(ks + 2 * X::kplane));
+            bf8 t[3];
+            split3_bf16(vst, t[0], t[1], t[2]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const U16B u = __builtin_bit_cast(U16B, t[p]);
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+                    if (slot_valid<D>(sg, x))
+                        vt[p * X::vplane + (chunk_start<D>(sg) + x) * kXVP + sslot] =
+                            uint16_t(u.w[x >> 1] >> (16 * (x & 1)));
+            }
+        }
+    };
+
+    bf8 qf[QT][3];
+    bool qfin = true;
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        float x[8];
+        load_chunk8<F32, D>(qu + int64_t(q0 + 16 * t + c) * D, g, x);
+        qfin = qfin && all_finite(x);
+        split3_bf16(x, qf[t][0], qf[t][1], qf[t][2]);
+    }
+    const bool qbad = __builtin_amdgcn_ballot_w64(!qfin) != 0;
+    f4 OT[QT][NCT];
+    float mref[QT], lsum[QT];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+            OT[t][ct] = f4{0.f, 0.f, 0.f, 0.f};
+        mref[t] = -INFINITY;
+        lsum[t] = 0.f;
+    }
+    // The reference point of query tile t when a score exceeds it by 2^8.
+    auto raise = [&](int t, float lmax) {
+        if (__builtin_amdgcn_ballot_w64(s2 * lmax > mref[t] + 8.f) != 0) {
+            const float mnew = fmaxf(mref[t], s2 * max_groups(lmax));
+            const float f = fast_exp2(mref[t] - mnew);
+            lsum[t] *= f;
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct)
+                OT[t][ct] *= f;
+            mref[t] = mnew;
+        }
+    };
+
+    const int nblk = N / kXB;
+    fetch(0);
+    store(0, 0);
+    __syncthreads();
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int buf = blk & 1;
+        if (blk + 1 < nblk)
+            fetch(blk + 1);
+        const unsigned char *bb = xsm + buf * X::bytes;
+        const uint16_t *ks = reinterpret_cast<const uint16_t *>(bb), *vt = ks + 3 * X::kplane;
+        const bool bad = qbad || __builtin_amdgcn_readfirstlane(
+                                     *reinterpret_cast<const int *>(bb + X::flag)) == blk;
+        if (!bad) {   // uniform
+#pragma unroll 1
+            for (int kp = 0; kp < 2; ++kp) {   // 32 keys
+                // K's terms are dead before V's are read (registers): the
+                // scores of every query tile first.
+                bf8 kv[2][3];
+                f4 st[QT][2];   // S^T[key 32kp+16h+4g+i][query q0+16t+c]
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        kv[h][p] = *reinterpret_cast<const bf8 *>(
+                            ks + p * X::kplane + (32 * kp + 16 * h + c) * kXKP + 8 * g);
+#pragma unroll
+                for (int t = 0; t < QT; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        st[t][h] = mfma_split3(kv[h][0], kv[h][1], kv[h][2], qf[t][0], qf[t][1],
+                                               qf[t][2], f4{0.f, 0.f, 0.f, 0.f});
+                __builtin_amdgcn_sched_barrier(0);
+                bf8 vf[NCT][3];
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        vf[ct][p] = *reinterpret_cast<const bf8 *>(
+                            vt + p * X::vplane + (16 * ct + c) * kXVP + 32 * kp + 8 * g);
+#pragma unroll
+                for (int t = 0; t < QT; ++t) {
+                    raise(t, fmaxf(fmaxf(fmaxf(st[t][0][0], st[t][0][1]),
+                                         fmaxf(st[t][0][2], st[t][0][3])),
+                                   fmaxf(fmaxf(st[t][1][0], st[t][1][1]),
+                                         fmaxf(st[t][1][2], st[t][1][3]))));
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            st[t][h][i] = fast_exp2(fmaf(s2, st[t][h][i], -mref[t]));
+                            lsum[t] += st[t][h][i];
+                        }
+                    bf8 ph, pm, pl;
+                    split3_prob(st[t][0], st[t][1], ph, pm, pl);
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct)
+                        OT[t][ct] = mfma_split3(vf[ct][0], vf[ct][1], vf[ct][2], ph, pm, pl,
+                                                OT[t][ct]);
+                }
+            }
+        } else {
+            for (int kt = 0; kt < 4; ++kt) {
+                const int key0 = blk * kXB + 16 * kt;
+                float kf[8];   // K row key0 + c, slots of group g
+                load_chunk8<F32, D>(ku + int64_t(key0 + c) * D, g, kf);
+                f4 vl[NCT];    // V[key0 + 4g + i][16ct + c]
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int f = 16 * ct + c;
+                        const float x = vu[int64_t(key0 + 4 * g + i) * D + (f < D ? f : D - 1)];
+                        vl[ct][i] = f < D ? x : 0.f;
+                    }
+#pragma unroll
+                for (int t = 0; t < QT; ++t) {
+                    float x[8];
+                    load_chunk8<F32, D>(qu + int64_t(q0 + 16 * t + c) * D, g, x);
+                    f4 st = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        st = mfma4(kf[e], x[e], st);
+                    raise(t, fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        st[i] = fast_exp2(fmaf(s2, st[i], -mref[t]));
+                        lsum[t] += st[i];
+                    }
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct)
+                        OT[t][ct] = mm16_acc(vl[ct], st, OT[t][ct]);
+                }
+            }
+        }
+        if (blk + 1 < nblk)
+            store(buf ^ 1, blk + 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        const float inv = __builtin_amdgcn_rcpf(sum_groups(lsum[t]));
+        float *orow = ou + int64_t(q0 + 16 * t + c) * D;
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int f = 16 * ct + 4 * g + i;
+                if (f < D)
+                    orow[f] = OT[t][ct][i] * inv;
+            }
+    }
+}
+
 // Query tiles per wave (four from 256 tokens on, so that a K or V fragment
 // read from LDS serves four products; one below, so that a workgroup still
 // has four waves to stage a block) and waves per workgroup.
@@ -636,8 +907,15 @@ void launch_exact_blocked_qt(const Problem &p, hipStream_t stream)
                            static_cast<const uint16_t *>(p.k), static_cast<const uint16_t *>(p.v),
                            static_cast<uint16_t *>(p.o), p.N, p.scale * kLog2e, wpu);
     } else {
-        const size_t lds = 2 * size_t(FBufs::bytes);
-        hipLaunchKernelGGL((exact_blocked_f32_kernel<D, QT>), dim3(unsigned(p.units * wpu)),
+        constexpr bool split = QT == 4;
+        const size_t lds = 2 * size_t(split ? SBufs::bytes : FBufs::bytes);
+        const auto kernel = [] {
+            if constexpr (split)
+                return exact_blocked_split_kernel<D, QT>;
+            else
+                return exact_blocked_f32_kernel<D, QT>;
+        }();
+        hipLaunchKernelGGL(kernel, dim3(unsigned(p.units * wpu)),
                            dim3(64 * nw), lds, stream, static_cast<const float *>(p.q),
                            static_cast<const float *>(p.k), static_cast<const float *>(p.v),
                            static_cast<float *>(p.o), p.N, p.scale * kLog2e, wpu);
