@@ -150,7 +150,8 @@ constexpr int table_den() { return 16 * MT * kTS; }
 // waves.  On return, after a workgroup barrier, W and W_D are in the table at
 // LargeLds::wb (W_D at offset table_den<MT>()).  FULL says m = 16 MT (every
 // landmark slot real), which folds the masks.
-template <int MT, int D, bool BFM, bool FULL = false>
+// RES selects the residual form of the fp32 iteration (see there).
+template <int MT, int D, bool BFM, bool FULL = false, bool RES = false>
 __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
                                               const f4 (&T)[2], float tden, int m, int iters,
                                               float s2, int lt, int lane)
@@ -321,12 +322,15 @@ __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
     __syncthreads();   // every wave has its Z_0 row (the T table may follow in Zb)
 
     // Iteration: X = A Z; Z <- Z (13I - X (15I - X (7I - X))) / 4, each wave
-    // producing its row tile of every product.
+    // producing its row tile of every product.  RES: the same polynomial in
+    // E = X - I, Z <- Z + Z (E (E - E E / 4) - E), also four products: near
+    // convergence the correction is small, where the constants of the other
+    // form round at 4 to 13 units of the diagonal.
     for (int it = 0; it < iters; ++it) {
         f4 X[MT];
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
-            f4 acc = zero4;
+            f4 acc = RES && j == lt ? -eye : zero4;   // RES: X holds E
 #pragma unroll
             for (int kk = 0; kk < MT; ++kk)
                 acc = mm16_acc(ALT[kk], read_r<P>(Zb, kk, j, g, c), acc);
@@ -354,11 +358,11 @@ __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
             f4 acc;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                acc[i] = fmaf(X[j][i], -7.f, j == lt ? 15.f * eye[i] : 0.f);
+                acc[i] = RES ? 0.f : fmaf(X[j][i], -7.f, j == lt ? 15.f * eye[i] : 0.f);
 #pragma unroll
             for (int kk = 0; kk < MT; ++kk)
                 acc = mm16_acc(XLT[kk], read_r<P>(Ya, kk, j, g, c), acc);
-            Y[j] = acc;
+            Y[j] = RES ? X[j] - 0.25f * acc : acc;
         }
 #pragma unroll
         for (int j = 0; j < MT; ++j)
@@ -366,11 +370,11 @@ __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
-            f4 acc = j == lt ? eye * -13.f : zero4;
+            f4 acc = !RES && j == lt ? eye * -13.f : zero4;
 #pragma unroll
             for (int kk = 0; kk < MT; ++kk)
                 acc = mm16_acc(XLT[kk], read_r<P>(Yb, kk, j, g, c), acc);
-            Y[j] = acc;
+            Y[j] = RES ? acc - X[j] : acc;
         }
 #pragma unroll
         for (int j = 0; j < MT; ++j)
@@ -383,7 +387,8 @@ __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
 #pragma unroll
             for (int kk = 0; kk < MT; ++kk)
                 acc = mm16_acc(ZLT[kk], read_r<P>(Ya, kk, j, g, c), acc);
-            Zn[j] = acc * -0.25f;
+            // RES: own rows of Zb, which only this wave writes
+            Zn[j] = RES ? read_r<P>(Zb, lt, j, g, c) + acc : acc * -0.25f;
         }
 #pragma unroll
         for (int j = 0; j < MT; ++j)
