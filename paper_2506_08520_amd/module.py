@@ -131,13 +131,16 @@ class SwinTransformerBlock(nn.Module):
                 n1.normalized_shape != (C,) or n2.normalized_shape != (C,)):
             return False
         hidden = fc1.weight.shape[0]
-        want = ((n1.weight, (C,)), (n1.bias, (C,)), (n2.weight, (C,)), (n2.bias, (C,)),
-                (fc1.weight, (hidden, C)), (fc2.weight, (C, hidden)), (fc1.bias, (hidden,)),
-                (fc2.bias, (C,)), (attn.w_qkv, (C, 3 * C)), (attn.b_qkv, (3 * C,)),
-                (attn.w_proj, (C, C)), (attn.b_proj, (C,)))
+        # The biases of the MLP may be absent; the norms' weights and biases may not.
+        want = [(n1.weight, (C,)), (n1.bias, (C,)), (n2.weight, (C,)), (n2.bias, (C,)),
+                (fc1.weight, (hidden, C)), (fc2.weight, (C, hidden)),
+                (attn.w_qkv, (C, 3 * C)), (attn.b_qkv, (3 * C,)),
+                (attn.w_proj, (C, C)), (attn.b_proj, (C,))]
+        if fc1.bias is not None:
+            want.append((fc1.bias, (hidden,)))
+        if fc2.bias is not None:
+            want.append((fc2.bias, (C,)))
         for t, shape in want:
-            if t is None and shape in ((hidden,), (C,)) and (t is fc1.bias or t is fc2.bias):
-                continue
             if (type(t) not in (nn.Parameter, torch.Tensor) or t.dtype != x.dtype or
                     t.device != x.device or tuple(t.shape) != shape or not t.is_contiguous()):
                 return False

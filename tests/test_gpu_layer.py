@@ -106,6 +106,19 @@ def test_no_biases():
     assert np.sqrt(((n64(blk(x)) - ref) ** 2).mean() / (ref ** 2).mean()) <= 1.3e-2
 
 
+@pytest.mark.parametrize("affine,biases", [(False, False), (False, True), (True, False)])
+def test_norms_without_parameters(affine, biases):
+    """LayerNorm without weight and bias, or without bias alone, is composed,
+    whatever biases the MLP has."""
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    kw = dict(dtype=torch.bfloat16, device="cuda")
+    blk.norm1 = nn.LayerNorm(64, elementwise_affine=affine, bias=False, **kw)
+    if not biases:
+        blk.mlp[0].bias = blk.mlp[2].bias = None
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    assert not blk._fusable(x) and torch.equal(blk(x), composed(blk, x))
+
+
 def test_weights_are_read_every_call():
     """Writes through .data (no version bump) to the norms and the MLP count."""
     blk = make(64, 2, 8, 4, 16, "nystrom")
