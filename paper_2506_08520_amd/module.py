@@ -16,6 +16,8 @@ nystra_layer_forward with the same weights.
 Relative-position bias and the shifted-window mask are not applied: Eqs.
 (1)-(8) have neither.
 """
+import math
+
 import torch
 from torch import nn
 
@@ -128,7 +130,8 @@ class SwinTransformerBlock(nn.Module):
         if (type(fc1) is not nn.Linear or type(act) is not nn.GELU or type(fc2) is not nn.Linear or
                 act.approximate != "none" or attn.dim != C or C > 256 or C % 4 != 0 or
                 attn.heads < 1 or (C // attn.heads) % 2 != 0 or
-                n1.normalized_shape != (C,) or n2.normalized_shape != (C,)):
+                n1.normalized_shape != (C,) or n2.normalized_shape != (C,) or
+                not (math.isfinite(n1.eps) and math.isfinite(n2.eps))):
             return False
         hidden = fc1.weight.shape[0]
         # The biases of the MLP may be absent; the norms' weights and biases may not.

@@ -119,6 +119,17 @@ def test_norms_without_parameters(affine, biases):
     assert not blk._fusable(x) and torch.equal(blk(x), composed(blk, x))
 
 
+@pytest.mark.parametrize("eps", [float("inf"), float("nan")])
+def test_eps_that_is_not_finite(eps):
+    """Refused by the C entry, so composed."""
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    blk.norm2.eps = eps
+    x = torch.randn(1, 16, 16, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    y, z = blk(x), composed(blk, x)
+    assert not blk._fusable(x) and torch.equal(torch.isnan(y), torch.isnan(z))
+    assert torch.equal(y.nan_to_num(), z.nan_to_num())
+
+
 def test_weights_are_read_every_call():
     """Writes through .data (no version bump) to the norms and the MLP count."""
     blk = make(64, 2, 8, 4, 16, "nystrom")
