@@ -167,14 +167,17 @@ class SwinTransformerBlock(nn.Module):
 
     def _forward_fused(self, x):
         attn, (fc1, _, fc2) = self.attn, self.mlp
-        x = x.contiguous()
-        ws, att = attn._workspace(x)
-        return B.nystra_layer_forward(
-            x, attn.w_qkv, attn.b_qkv, attn.w_proj, attn.b_proj, attn._packed_weights(),
+        xc = x.contiguous()
+        ws, att = attn._workspace(xc)
+        y = B.nystra_layer_forward(
+            xc, attn.w_qkv, attn.b_qkv, attn.w_proj, attn.b_proj, attn._packed_weights(),
             (self.norm1.weight, self.norm1.bias, self.norm1.eps),
             (self.norm2.weight, self.norm2.bias, self.norm2.eps), fc1.weight, fc1.bias,
             fc2.weight, fc2.bias, attn.heads, attn.window, shift=attn.shift, m=attn.m,
             opts=attn.opts, attention=att, workspace=ws)
+        # A residual sum lays its result out as x lies (densely, in x's order
+        # of the dimensions), so the fused result does too.
+        return y if xc is x else torch.empty_like(x).copy_(y)
 
     @torch.no_grad()
     def forward(self, x):

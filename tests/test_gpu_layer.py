@@ -130,6 +130,23 @@ def test_eps_that_is_not_finite(eps):
     assert torch.equal(y.nan_to_num(), z.nan_to_num())
 
 
+@pytest.mark.parametrize("layout", ["channels first", "transposed", "slice", "rows", "expanded"])
+def test_layout_of_the_result(layout):
+    """The result lies in memory as the composition's does."""
+    blk = make(64, 2, 8, 4, 16, "nystrom")
+    g = torch.Generator().manual_seed(7)
+    x = torch.randn(2, 64, 16, 24, generator=g).bfloat16().cuda()
+    x = {"channels first": lambda: x.permute(0, 2, 3, 1),
+         "transposed": lambda: x.permute(0, 2, 3, 1).contiguous().transpose(1, 2),
+         "slice": lambda: torch.cat([x, x], 1).permute(0, 2, 3, 1).contiguous()[..., 64:],
+         "rows": lambda: x.permute(0, 3, 2, 1).contiguous()[:, ::3],
+         "expanded": lambda: x[:1].permute(0, 2, 3, 1).contiguous().expand(3, 16, 24, 64)}[layout]()
+    assert not x.is_contiguous() and blk._fusable(x)
+    y = blk(x)
+    assert y.stride() == composed(blk, x).stride()
+    assert torch.equal(y, blk(x.contiguous()))
+
+
 def test_weights_are_read_every_call():
     """Writes through .data (no version bump) to the norms and the MLP count."""
     blk = make(64, 2, 8, 4, 16, "nystrom")
