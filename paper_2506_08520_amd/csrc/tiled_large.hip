@@ -54,10 +54,12 @@ struct LargeArgs {
 // their logits become -inf and their V rows 0 after the products, and their O
 // rows are not stored.  The extra index arithmetic is paid only here, so
 // multiples of 16 keep the kernels without it.  10 x 10 windows, m = 25,
-// d_h = 16, 3072 fp32 units: 1267 us in the generic kernel, 85.5 us here.  The
-// fp32 form also orders its sums for accuracy (pairs of tiles summed apart,
-// the residual form of Step 4, a refined reciprocal); that costs 0.3 us and
-// takes the error against 64 bits from 2.7e-7 to 1.9e-7 (generic: 2.1e-7).
+// d_h = 16, 3072 fp32 units: 1267 us in the generic kernel, 85.5 us here.  Its
+// sums are ordered for accuracy (pairs of tiles summed apart, the residual form
+// of Step 4, a refined reciprocal); that costs 0.3 us and takes the fp32 error
+// against 64 bits from 2.7e-7 to 1.9e-7 (generic: 2.1e-7).  bf16 inputs run the
+// same fp32 products, as the generic kernel does: two-term bf16 operands carry
+// 16 bits of what is held in 24 there.
 template <class E, int MT, int D, bool BFM, bool FULL, int KPL, bool RAG = false>
 __global__ void __launch_bounds__(64 * MT)
 __attribute__((amdgpu_waves_per_eu(KPL == 1 ? 4 : 1)))
@@ -68,6 +70,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
     using L = LargeLds<MT>;
     constexpr bool KP = KPL != 0;
     static_assert(!KP || (BFM && FULL), "K pooling in the key pass: bf16, full landmark tiles");
+    static_assert(!RAG || !BFM, "a partial tile: fp32 products, whatever the inputs");
     constexpr int d = D;
     // With a spare column (D % 16 != 0), column D of V is replaced by ones, so
     // that column D of T, W and O carries T_D, W_D and O_D (no separate sums).
@@ -283,19 +286,9 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
 #pragma unroll
                     for (int x = 0; x < 4; ++x)
                         at[x] = unsigned(min(16 * tt + 4 * g + x, N - 1)) * d + f0;
-                    if constexpr (BFM) {
 #pragma unroll
-                        for (int pp = 0; pp < 2; ++pp) {
-                            u16x2 pr;
-                            pr.x = vu16[at[2 * pp]];
-                            pr.y = vu16[at[2 * pp + 1]];
-                            vh_[u][ct][pp] = __builtin_bit_cast(uint32_t, pr);
-                        }
-                    } else {
-#pragma unroll
-                        for (int x = 0; x < 4; ++x)
-                            vr_[u][ct][x] = E::load(vu, at[x]);
-                    }
+                    for (int x = 0; x < 4; ++x)
+                        vr_[u][ct][x] = E::load(vu, at[x]);
                 } else if constexpr (BFM) {
 #pragma unroll
                     for (int pp = 0; pp < 2; ++pp) {
@@ -341,18 +334,10 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
-                    if constexpr (BFM) {
+                for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-                        for (int pp = 0; pp < 2; ++pp)
-                            vh_[u][ct][pp] &= (4 * g + 2 * pp < vend[u] ? 0xffffu : 0u) |
-                                              (4 * g + 2 * pp + 1 < vend[u] ? 0xffff0000u : 0u);
-                    } else {
-#pragma unroll
-                        for (int x = 0; x < 4; ++x)
-                            vr_[u][ct][x] = 4 * g + x < vend[u] ? vr_[u][ct][x] : 0.f;
-                    }
-                }
+                    for (int x = 0; x < 4; ++x)
+                        vr_[u][ct][x] = 4 * g + x < vend[u] ? vr_[u][ct][x] : 0.f;
         }
         bf8 vv[NCT];   // bf16 path: V of the pair as the right-hand operand
         if constexpr (BFM) {
@@ -606,7 +591,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         else
             qbl[s] = qb[s];
     }
-    landmark_core<MT, D, BFM, FULL, RAG && !BFM>(lds, qbl, mu, T, tden, m, a.iters, a.s2, lt, lane);
+    landmark_core<MT, D, BFM, FULL, RAG>(lds, qbl, mu, T, tden, m, a.iters, a.s2, lt, lane);
     constexpr int TDo = table_den<MT>();
     float *Wb = lds + L::wb;
 
@@ -750,7 +735,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 for (int i = 0; i < 4; ++i)
                     rcp[i] = __builtin_amdgcn_rcpf(row_bcast<D % 16>(ont[D / 16][i]));
             }
-            if constexpr (RAG && E::bytes == 4) {
+            if constexpr (RAG) {
                 // One Newton step (v_rcp_f32 is within 1 ulp, not rounded): the
                 // kernel this path replaces divided.  1 / 0 and 1 / inf stay.
 #pragma unroll
@@ -854,7 +839,7 @@ void launch_large(const Problem &p, const LargeArgs &a, hipStream_t stream)
 {
     if (p.N % 16 != 0) {
         const size_t lds = size_t(LargeLds<MT>::total) * sizeof(float);
-        hipLaunchKernelGGL((tiled_large_kernel<E, MT, D, E::bytes == 2, false, 0, true>),
+        hipLaunchKernelGGL((tiled_large_kernel<E, MT, D, false, false, 0, true>),
                            dim3(unsigned(p.units)), dim3(64 * MT), lds, stream,
                            static_cast<const typename E::T *>(p.q),
                            static_cast<const typename E::T *>(p.k),

@@ -46,6 +46,21 @@ def test_ragged(shape, dtype):
     check(got, ref, dtype, f"ragged {shape} {dtype}")
 
 
+@pytest.mark.parametrize("shape", [(40, 2, 49, 30, 7, 0), (20, 2, 100, 16, 25, 0),
+                                   (8, 2, 196, 32, 49, 0), (20, 1, 126, 24, 9, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_bf16_is_computed_in_fp32(shape):
+    """bf16 inputs, fp32 arithmetic: past the rounding of the stored result, the
+    error is that of fp32 sums (at most 1e-5 of RMS over these shapes: a few
+    hundred roundings of 6e-8), where 16-bit operands measure 4e-5 and more."""
+    nw, h, N, d, m, mode = shape
+    q, k, v = W.iid((nw, h, N, d), seed=N * 17 + d + m, dtype="bf16")
+    ref = oracle.forward(q, k, v, m, iters=6, mode=mode)
+    t = [to_dev(x, "bf16") for x in (q, k, v)]
+    got = to_host(B.nystra_attn_forward_ex(*t, m, opts=B.make_opts(landmark_mode=mode)))
+    check(got, ref, "bf16", f"ragged {shape} bf16", beyond_bar=1e-5)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_neighbours_untouched(dtype):
     """Rows past a unit's last token are the next unit's: outputs of every unit
