@@ -324,17 +324,20 @@ __device__ inline void landmark_core(float *lds, const float (&qb)[8], float mu,
     // Iteration: X = A Z; Z <- Z (13I - X (15I - X (7I - X))) / 4, each wave
     // producing its row tile of every product.  RES: the same polynomial in
     // E = X - I, Z <- Z + Z (E (E - E E / 4) - E), also four products: near
-    // convergence the correction is small, where the constants of the other
-    // form round at 4 to 13 units of the diagonal.
+    // convergence the correction is small, where the sums of the other form
+    // start from 13 to 15 units of the diagonal and round there.
     for (int it = 0; it < iters; ++it) {
         f4 X[MT];
 #pragma unroll
         for (int j = 0; j < MT; ++j) {
-            f4 acc = RES && j == lt ? -eye : zero4;   // RES: X holds E
+            // RES: X holds E.  One landmark tile takes the identity off last (its
+            // error against 64 bits is a tenth lower so), more begin with it, which
+            // is 2% faster (10 x 10 windows, m = 25).
+            f4 acc = RES && MT > 1 && j == lt ? -eye : zero4;
 #pragma unroll
             for (int kk = 0; kk < MT; ++kk)
                 acc = mm16_acc(ALT[kk], read_r<P>(Zb, kk, j, g, c), acc);
-            X[j] = acc;
+            X[j] = RES && MT == 1 ? acc - eye : acc;
         }
         // own-row transpose of X through Yb (free at this point)
 #pragma unroll

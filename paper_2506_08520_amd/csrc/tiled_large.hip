@@ -54,12 +54,14 @@ struct LargeArgs {
 // their logits become -inf and their V rows 0 after the products, and their O
 // rows are not stored.  The extra index arithmetic is paid only here, so
 // multiples of 16 keep the kernels without it.  10 x 10 windows, m = 25,
-// d_h = 16, 3072 fp32 units: 1267 us in the generic kernel, 85.5 us here.  Its
-// sums are ordered for accuracy (pairs of tiles summed apart, the residual form
-// of Step 4, a refined reciprocal); that costs 0.3 us and takes the fp32 error
-// against 64 bits from 2.7e-7 to 1.9e-7 (generic: 2.1e-7).  bf16 inputs run the
-// same fp32 products, as the generic kernel does: two-term bf16 operands carry
-// 16 bits of what is held in 24 there.
+// d_h = 16, 3072 fp32 units: 1267 us in the generic kernel, 86 us here.  Its sums
+// are ordered for accuracy (pairs of tiles summed apart, the residual form of Step
+// 4, a refined reciprocal; one landmark tile as described at FOLD): over 308 shapes
+// of 9 to 1000 tokens and 1 to 49 landmarks the fp32 error against 64 bits is 0.99
+// of the generic kernel's on average and 1.10 at most (by the median unit; plain sums
+// gave 1.34 to 1.52 at m = 1 and 2), which costs up to 11% (N = 9801, m = 9, d_h = 30, 6
+// units: 783 -> 865 us).  bf16 inputs run the same fp32 products, as the generic
+// kernel does: two-term bf16 operands carry 16 bits of what is held in 24 there.
 template <class E, int MT, int D, bool BFM, bool FULL, int KPL, bool RAG = false>
 __global__ void __launch_bounds__(64 * MT)
 __attribute__((amdgpu_waves_per_eu(KPL == 1 ? 4 : 1)))
@@ -211,6 +213,31 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         tdj[j] = 0.f;
         mrj[j] = -INFINITY;
     }
+    // RAG, one landmark tile: the sums are folded into TO every two pairs, the
+    // rounding of each fold carried to the next in TC, so that a sum over many keys
+    // is no long chain of roundings.  (With more tiles the error is that of Step 4.)
+    constexpr bool FOLD = RAG && MT == 1;
+    f4 TO[NCT], TC[NCT];
+    float tdo = 0.f;
+    int folded = 0;
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+            TO[ct] = TC[ct] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto fold = [&]() {
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) {
+            const f4 y = TJ[0][ct] + TC[ct], t = TO[ct] + y, r = y - (t - TO[ct]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                TC[ct][i] = fabsf(r[i]) < INFINITY ? r[i] : 0.f;   // t not finite: t stays
+            TO[ct] = t;
+            TJ[0][ct] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        tdo += tdj[0];   // 64 partial sums of T_D (unless PAD)
+        tdj[0] = 0.f;
+    };
     // The wave's key tile pairs: t0 = t_begin, t_begin + t_stride, ... below
     // t_end.  Round-robin over the waves, or (KP) a contiguous block of whole
     // patch bands: ppb pairs of tiles cover the rows of one band of patches.
@@ -389,6 +416,14 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct)
                     TJ[j][ct] *= fr;
+                if constexpr (FOLD) {
+                    tdo *= f;
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) {
+                        TO[ct] *= fr;
+                        TC[ct] *= fr;
+                    }
+                }
             }
             mrj[j] = mnew;
             // Landmarks past m get an infinite offset: their terms are exactly 0.
@@ -412,6 +447,31 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                     TJ[j][ct] = mfma_bf16(gh, vv[ct], TJ[j][ct]);
                     TJ[j][ct] = mfma_bf16(gl, vv[ct], TJ[j][ct]);
                 }
+            } else if constexpr (FOLD) {
+                // The pair's 32 keys as a tree: eight products of four keys each,
+                // then in pairs, then onto the sums so far.  Absent keys add zeros.
+                auto tree = [](const auto (&p)[2][4]) {
+                    return ((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) +
+                           ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3]));
+                };
+                float e[2][4];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        e[u][i] = fast_exp2(fmaf(a.s2, su[u][i], -mb));
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    f4 part[2][4];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int x = 0; x < 4; ++x)
+                            part[u][x] = mfma4(e[u][x], vr_[u][ct][x], f4{0.f, 0.f, 0.f, 0.f});
+                    TJ[j][ct] += tree(part);
+                }
+                if constexpr (!PAD)
+                    tdj[j] += tree(e);
             } else {
                 // RAG: the pair's 32 keys are summed by themselves and then
                 // added, so that a sum over many keys is two short chains of
@@ -444,6 +504,10 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 if constexpr (RAG && !PAD)
                     tdj[j] += tp;
             }
+        }
+        if constexpr (FOLD) {
+            if (++folded % 2 == 0)   // uniform
+                fold();
         }
         if constexpr (KP) {
             // Step 1 for K.  The product K_tile x ksel (tile ct) puts K[token
@@ -518,6 +582,13 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                         vh[u][ct][x] = vhn[u][ct][x];
             }
         }
+    }
+    if constexpr (FOLD) {
+        fold();
+        tdj[0] = tdo;
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+            TJ[0][ct] = TO[ct];
     }
     // This wave's record: T rows of every landmark, T_D and the maxima.  An
     // idle wave (fewer key pairs than waves) leaves -inf maxima, which the
@@ -735,16 +806,26 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                 for (int i = 0; i < 4; ++i)
                     rcp[i] = __builtin_amdgcn_rcpf(row_bcast<D % 16>(ont[D / 16][i]));
             }
+            // RAG: v_rcp_f32 is within 1 ulp, not rounded, and the kernel this path
+            // replaces divided.  One Newton step, or with one landmark tile each
+            // quotient corrected by its remainder.  0, infinities and NaN stay.
             if constexpr (RAG) {
-                // One Newton step (v_rcp_f32 is within 1 ulp, not rounded): the
-                // kernel this path replaces divided.  1 / 0 and 1 / inf stay.
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float od = PAD ? row_bcast<D % 16>(ont[D / 16 % 2][i]) : odv[i];
-                    const float e = fmaf(-od, rcp[i], 1.f);
-                    rcp[i] = fabsf(e) < 0.5f ? fmaf(e, rcp[i], rcp[i]) : rcp[i];
+                    if constexpr (PAD)
+                        odv[i] = row_bcast<D % 16>(ont[D / 16 % 2][i]);
+                    const float e = fmaf(-odv[i], rcp[i], 1.f);
+                    if constexpr (!FOLD)
+                        rcp[i] = fabsf(e) < 0.5f ? fmaf(e, rcp[i], rcp[i]) : rcp[i];
                 }
             }
+            auto quot = [&](float n, int i) {
+                const float x = n * rcp[i];
+                if constexpr (!FOLD)
+                    return x;
+                const float r = fmaf(-x, odv[i], n);
+                return fabsf(r) <= fabsf(n) ? fmaf(r, rcp[i], x) : x;
+            };
 #pragma unroll
             for (int ct = 0; ct < 2; ++ct) {
                 const f4 on = ont[ct];
@@ -753,15 +834,15 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         if (16 * tt + 4 * g + i < N)
-                            E::store(ou, int64_t(16 * tt + 4 * g + i) * d + f, on[i] * rcp[i]);
+                            E::store(ou, int64_t(16 * tt + 4 * g + i) * d + f, quot(on[i], i));
                 } else if (f < d) {
                     const int64_t orow = int64_t(16 * tt + 4 * g) * d + f;
                     if constexpr (E::bytes == 2) {
                         // rows (0, 1) and (2, 3) converted in pairs (round to
                         // nearest even), stored as 16-bit values
                         uint16_t *o16 = reinterpret_cast<uint16_t *>(ou) + orow;
-                        const uint32_t p01 = cvt_bf16x2(on[0] * rcp[0], on[1] * rcp[1]);
-                        const uint32_t p23 = cvt_bf16x2(on[2] * rcp[2], on[3] * rcp[3]);
+                        const uint32_t p01 = cvt_bf16x2(quot(on[0], 0), quot(on[1], 1));
+                        const uint32_t p23 = cvt_bf16x2(quot(on[2], 2), quot(on[3], 3));
                         o16[0] = uint16_t(p01);
                         o16[d] = uint16_t(p01 >> 16);
                         o16[2 * d] = uint16_t(p23);
@@ -769,7 +850,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                     } else {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            E::store(ou, orow + i * d, on[i] * rcp[i]);
+                            E::store(ou, orow + i * d, quot(on[i], i));
                     }
                 }
             }

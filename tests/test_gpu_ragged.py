@@ -61,6 +61,47 @@ def test_bf16_is_computed_in_fp32(shape):
     check(got, ref, "bf16", f"ragged {shape} bf16", beyond_bar=1e-5)
 
 
+@pytest.mark.parametrize("N,d,m", [(36, 24, 1), (36, 20, 6), (49, 24, 7), (100, 24, 1),
+                                   (100, 16, 25), (225, 30, 9), (900, 30, 1), (900, 30, 2)])
+def test_error_is_the_generic_kernels(N, d, m):
+    """fp32: the median over 512 units of a unit's error against 64 bits, beside that
+    of the generic kernel.  Both are a few roundings of 6e-8; 15% is what the median
+    moves with another draw (3%) and what shapes differ by either way (10%), where
+    one chain of roundings over the keys measures 1.4 to 1.7."""
+    side = int(round(N ** 0.5))
+    g = torch.Generator().manual_seed(N + d + m)
+    q, k, v = (torch.randn(512, 1, N, d, generator=g) for _ in range(3))
+    rows = [n for n in range(1, m + 1) if m % n == 0 and side % n == 0 and side % (m // n) == 0]
+    gc = max(n for n in rows if n * n <= m)
+    gr = m // gc
+
+    def pool(x):
+        x = x.view(512, gr, side // gr, gc, side // gc, d)
+        return x.mean((2, 4)).reshape(512, m, d)
+
+    q6, k6, v6 = (t.double()[:, 0] for t in (q, k, v))
+    s, qb, kb = d ** -0.5, pool(q6), pool(k6)
+    su = s * (qb @ k6.transpose(1, 2))
+    mu = su.amax(2, keepdim=True)
+    gu, a = torch.exp(su - mu), torch.exp(s * (qb @ kb.transpose(1, 2)) - mu)
+    z = a.transpose(1, 2) / (a.sum(1).amax(1) * a.sum(2).amax(1)).view(-1, 1, 1)
+    eye = torch.eye(m, dtype=a.dtype)
+    for _ in range(6):
+        x = a @ z
+        z = 0.25 * (z @ (13 * eye - x @ (15 * eye - x @ (7 * eye - x))))
+    gl = torch.softmax(s * (q6 @ kb.transpose(1, 2)), 2)
+    ref = (gl @ (z @ (gu @ v6))) / (gl @ (z @ gu.sum(2, keepdim=True)))
+    err = {}
+    for variant in (B.VARIANT_GENERIC, B.VARIANT_AUTO):
+        o = B.nystra_attn_forward_ex(q.cuda(), k.cuda(), v.cuda(), m,
+                                     opts=B.make_opts(variant=variant)).cpu().double()[:, 0]
+        e = (o - ref).square().sum((1, 2)) / ref.square().sum((1, 2))
+        err[variant] = e.sqrt().median().item()
+    ratio = err[B.VARIANT_AUTO] / err[B.VARIANT_GENERIC]
+    print(f"ragged N={N} d={d} m={m}: {err[B.VARIANT_AUTO]:.2e}, {ratio:.2f} of the generic kernel's")
+    assert ratio <= 1.15
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_neighbours_untouched(dtype):
     """Rows past a unit's last token are the next unit's: outputs of every unit
