@@ -62,6 +62,8 @@ struct LargeArgs {
 // gave 1.34 to 1.52 at m = 1 and 2), which costs up to 11% (N = 9801, m = 9, d_h = 30, 6
 // units: 783 -> 865 us).  bf16 inputs run the same fp32 products, as the generic
 // kernel does: two-term bf16 operands carry 16 bits of what is held in 24 there.
+// Infinite and NaN inputs give what they give in the generic kernel: keys masked
+// with -inf weigh nothing, a value reaches its own column only.
 template <class E, int MT, int D, bool BFM, bool FULL, int KPL, bool RAG = false>
 __global__ void __launch_bounds__(64 * MT)
 __attribute__((amdgpu_waves_per_eu(KPL == 1 ? 4 : 1)))
@@ -87,11 +89,12 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
     const int m = FULL ? 16 * MT : a.m, N = a.N, NT = RAG ? (a.N + 15) >> 4 : a.N >> 4;
     const int l = 16 * lt + c;            // this lane's landmark
     // exp(s (x - y)) of two running maxima.  RAG takes the rounded s x and s y
-    // that the logits are offset by, so that their rounding cancels.
+    // that the logits are offset by, so that their rounding cancels, and 1 for
+    // equal ones, -inf (only masked keys so far) among them.
     auto max_ratio = [&](float x, float y) {
         if constexpr (RAG) {
             const float sx = __fmul_rn(a.s2, x), sy = __fmul_rn(a.s2, y);
-            return fast_exp2(__fsub_rn(sx, sy));
+            return x == y ? 1.f : fast_exp2(__fsub_rn(sx, sy));
         }
         return fast_exp2(a.s2 * (x - y));
     };
@@ -353,6 +356,14 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                         vr_[u][ct][x] = f < d ? vr_[u][ct][x] : (PAD && f == d ? 1.f : 0.f);
                 }
             }
+        if constexpr (RAG && E::bytes == 4) {
+            // An infinity must not meet the zeros of Qbar's overlapping slots.
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+                    kr_[u][x] = slot_keep<D>(g, x) ? kr_[u][x] : 0.f;
+        }
         const bool second = t0 + 1 < NT;   // uniform
         // RAG: keys of tile u from here on (4g + i >= vend[u]) are absent
         const bool partial = RAG && 16 * (t0 + 2) > N;   // uniform
@@ -427,7 +438,9 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
             }
             mrj[j] = mnew;
             // Landmarks past m get an infinite offset: their terms are exactly 0.
-            const float mb = (FULL || 16 * j + c < m) ? a.s2 * mnew : INFINITY;
+            // RAG: nor has a landmark an offset while every key of its is masked.
+            const float mb = !(FULL || 16 * j + c < m) ? INFINITY
+                             : RAG && mnew == -INFINITY ? 0.f : a.s2 * mnew;
             if constexpr (BFM) {
                 // bf16 product over the 32 keys of the pair, lane group g
                 // supplying keys 4g..4g+3 of both tiles (N % 32 == 0 here)
@@ -648,6 +661,14 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         }
     }
     const float mu = a.s2 * mrun;   // m_U of landmark l (base-2 units)
+    if constexpr (RAG) {
+        // Landmarks past m: an infinite K or V row made NaN of their zeros.
+        tden = lval ? tden : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (16 * lt + 4 * g + i >= m)
+                T[0][i] = T[1][i] = 0.f;
+    }
 
     // This lane's Qbar row, read back from its table (intact until the core
     // overwrites the region, after its first barrier) rather than held in
@@ -675,6 +696,12 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         WR[kk][0] = read_r<kTS>(Wb, kk, 0, g, c);
         WR[kk][1] = read_r<kTS>(Wb, kk, 1, g, c);
         wdv[kk] = *reinterpret_cast<const f4 *>(Wb + TDo + 16 * kk + 4 * g);
+        if constexpr (RAG) {   // as T: Z's zeros times an infinity
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (16 * kk + 4 * g + i >= m)
+                    WR[kk][0][i] = WR[kk][1][i] = wdv[kk][i] = 0.f;
+        }
 #pragma unroll
         for (int s = 0; s < 8; ++s)
             kb[kk][s] = slot_valid<D>(g, s)

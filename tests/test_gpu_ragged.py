@@ -118,6 +118,37 @@ def test_neighbours_untouched(dtype):
         assert torch.equal(alone[0], out[u])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,d,m,mode", [(36, 12, 1, 0), (49, 30, 7, 0), (49, 16, 7, 0),
+                                        (100, 16, 25, 0), (100, 20, 25, 0), (196, 32, 49, 0),
+                                        (105, 24, 35, 1)])
+def test_values_that_are_not_finite(N, d, m, mode, dtype):
+    """-inf keys mask, as do keys of the type's lowest value: the first tokens (whole
+    pairs of tiles of a wave), the last ones, single ones.  Infinities and NaN in V reach their
+    column and nothing else.  Everything as the generic kernel gives it."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(N + d + m)
+    q, k, v = (torch.randn(8, 1, N, d, generator=g) for _ in range(3))
+    q = q.abs() + 0.5
+    side = int(round(N ** 0.5))
+    low = torch.finfo(tdt).min
+    third = (N // 3 // side) * side if mode == 0 else N // 3
+    # every feature, the first only, the last only: each slot of a chunk of eight
+    k[0, :, :third], k[1, :, :third, 0], k[2, :, N - 1, d - 1] = -np.inf, -np.inf, -np.inf
+    k[3, :, min(40, N // 2):], k[4, :, 5] = -np.inf, low
+    v[5, :, N - 2, 3], v[6, :, 1, d - 1] = np.inf, np.nan
+    t = [x.to(tdt).cuda() for x in (q, k, v)]
+    got, ref = (B.nystra_attn_forward_ex(*t, m, opts=B.make_opts(landmark_mode=mode, variant=var))
+                .float().cpu() for var in (B.VARIANT_AUTO, B.VARIANT_GENERIC))
+    assert torch.isfinite(ref[7]).all() and (m == 1 or torch.isfinite(ref[0]).all())
+    for u in range(8):
+        same = torch.equal(torch.isnan(got[u]), torch.isnan(ref[u])) and \
+            torch.equal(got[u][torch.isinf(ref[u])], ref[u][torch.isinf(ref[u])])
+        ok = torch.isfinite(ref[u])
+        near = same and torch.allclose(got[u][ok], ref[u][ok], rtol=2e-2, atol=2e-2)
+        assert near, f"unit {u}: {int(torch.isnan(got[u]).sum())} NaN, {int(torch.isnan(ref[u]).sum())} expected"
+
+
 def test_named_variants_unchanged():
     """AUTO takes the tiled kernel; by name such shapes stay GENERIC only."""
     assert B.nystra_select_variant(100, 16, 25) == B.VARIANT_GENERIC
