@@ -14,6 +14,8 @@
 // current one is multiplied; four waves each own a 32 x 32 quarter (2 x 2
 // MFMA tiles).  Blocks are mapped so that the column tiles of one row tile
 // run on the same XCD and share its L2 for the gathered rows.
+#include <type_traits>
+
 #include "block_common.hpp"
 
 namespace nystra {
@@ -235,6 +237,11 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
     constexpr bool BF = F::BF;
     constexpr int kSlots = F::BM * F::slots;     // slots of one operand plane
     __shared__ bf8 As[F::planes * kSlots], Bs[F::planes * kSlots];
+    // fp32: a value of A or W is not finite; the tile is then computed again on the
+    // fp32 matrix cores.
+    __shared__ int infinite;
+    if (!BF && threadIdx.x == 0)
+        infinite = 0;
     int rt, ct;
     tile_of(a, rt, ct);
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -295,6 +302,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
             rb[e].w[1] = ok ? x.w[1] : 0u;
         }
     };
+    u16x2 top = {0, 0};
     auto stash = [&]() {
 #pragma unroll
         for (int j = 0; j < F::ap; ++j) {
@@ -306,7 +314,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     x[e] = __uint_as_float(ra[j][e >> 2].w[e & 3]);
-                split3_bf16(x, As[at], As[kSlots + at], As[2 * kSlots + at]);
+                split3_bf16(x, As[at], As[kSlots + at], As[2 * kSlots + at], top);
             }
         }
 #pragma unroll
@@ -324,48 +332,65 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     x[e] = __uint_as_float(rb[e].w[j]);
-                split3_bf16(x, Bs[at], Bs[kSlots + at], Bs[2 * kSlots + at]);
+                split3_bf16(x, Bs[at], Bs[kSlots + at], Bs[2 * kSlots + at], top);
             }
         }
     };
 
     f4 acc[4][4];   // [row tile][column tile]: lane (g, c) row c, columns 4g + i
+    auto product = [&](auto f32) {   // f32: on the fp32 matrix cores
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    fetch(0);
-    for (int k0 = 0; k0 < a.C; k0 += F::BK) {
-        stash();
-        __syncthreads();
-        if (k0 + F::BK < a.C)   // uniform
-            fetch(k0 + F::BK);
+            for (int j = 0; j < 4; ++j)
+                acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        fetch(0);
+        for (int k0 = 0; k0 < a.C; k0 += F::BK) {
+            stash();
+            __syncthreads();
+            if (k0 + F::BK < a.C)   // uniform
+                fetch(k0 + F::BK);
 #pragma unroll
-        for (int s = 0; s < F::BK / 32; ++s) {
-            bf8 av[4][F::planes];
+            for (int s = 0; s < F::BK / 32; ++s) {
+                bf8 av[4][F::planes];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int p = 0; p < F::planes; ++p)
-                    av[i][p] = As[p * kSlots + wide_slot<E>(64 * wr + 16 * i + c, 4 * s + g)];
+                    for (int p = 0; p < F::planes; ++p)
+                        av[i][p] = As[p * kSlots + wide_slot<E>(64 * wr + 16 * i + c, 4 * s + g)];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bf8 bv[F::planes];
+                for (int j = 0; j < 4; ++j) {
+                    bf8 bv[F::planes];
 #pragma unroll
-                for (int p = 0; p < F::planes; ++p)
-                    bv[p] = Bs[p * kSlots + wide_slot<E>(64 * wc + 16 * j + c, 4 * s + g)];
+                    for (int p = 0; p < F::planes; ++p)
+                        bv[p] = Bs[p * kSlots + wide_slot<E>(64 * wc + 16 * j + c, 4 * s + g)];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if constexpr (BF)
-                        acc[i][j] = mfma_bf16(bv[0], av[i][0], acc[i][j]);
-                    else
-                        acc[i][j] = mfma_split3(bv[0], bv[1], bv[2], av[i][0], av[i][1], av[i][2],
-                                                acc[i][j]);
+                    for (int i = 0; i < 4; ++i) {
+                        if constexpr (BF) {
+                            acc[i][j] = mfma_bf16(bv[0], av[i][0], acc[i][j]);
+                        } else if constexpr (f32) {
+                            float x[8], w[8];
+                            join3_bf16(av[i][0], av[i][1], av[i][2], x);
+                            join3_bf16(bv[0], bv[1], bv[2], w);
+                            acc[i][j] = mfma_f32x8(w, x, acc[i][j]);
+                            __builtin_amdgcn_sched_barrier(0);   // few registers
+                        } else {
+                            acc[i][j] = mfma_split3(bv[0], bv[1], bv[2], av[i][0], av[i][1],
+                                                    av[i][2], acc[i][j]);
+                        }
+                    }
                 }
             }
+            __syncthreads();
         }
+    };
+    product(std::false_type{});
+    if constexpr (!BF) {
+        if (not_finite(top))
+            infinite = 1;
         __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(infinite))   // uniform
+            product(std::true_type{});
     }
 
     // Epilogue: four adjacent columns of one row per lane and tile, in one head
@@ -539,6 +564,39 @@ __device__ inline void tile_product(const bf8 (&ab)[L::NP][KS], const uint16_t *
     }
 }
 
+// The same on the fp32 matrix cores, for operands that are not all finite.
+template <class L, int KS>
+__device__ inline void tile_product_f32(const bf8 (&ab)[L::NP][KS], const uint16_t *h, int step,
+                                        f4 (&acc)[L::CT / 16])
+{
+#pragma unroll
+    for (int q = 0; q < L::CT / 16; ++q)
+        acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        // Joined here, on this rare path: the compiler must not keep the joined
+        // rows in registers over the tiles.
+        bf8 t[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            t[p] = ab[p % L::NP][s];
+            asm volatile("" : "+v"(t[p]));
+        }
+        float x[8];
+        join3_bf16(t[0], t[1], t[2], x);
+#pragma unroll
+        for (int q = 0; q < L::CT / 16; ++q) {
+            const uint16_t *w = &h[16 * q * L::PH + step * s];
+            float y[8];
+            join3_bf16(*reinterpret_cast<const bf8 *>(w),
+                       *reinterpret_cast<const bf8 *>(w + 2 * L::plane),
+                       *reinterpret_cast<const bf8 *>(w + 4 * L::plane), y);
+            acc[q] = mfma_f32x8(x, y, acc[q]);
+            __builtin_amdgcn_sched_barrier(0);   // few registers
+        }
+    }
+}
+
 // Stores a tile of CT columns from column n0 on: lane (g, c) holds rows 4g + i,
 // column c of each 16 x 16 tile; destination = row part (rowoff) + column part
 // (coltab).  With a.pair, lanes c and c ^ 1 swap one value per two rows so that
@@ -594,9 +652,13 @@ __device__ inline void store_tile(const BlockArgs &a, const f4 (&acc)[L::CT / 16
 // they are in registers -- a row's quarters lie in the four lane groups, so its
 // sums take two cross-lane steps -- and rounded to bf16 as the norm's own output
 // would be: the map is neither written nor read in between.
+// Four waves per SIMD, so two workgroups per CU, where the registers allow it.
+template <class E, bool PROJ, int KP, bool LN>
+constexpr int rk_waves() { return LN || (E::bytes == 4 && (KP > 128 || (PROJ && KP == 128))) ? 2 : 4; }
+
 template <class E, bool PROJ, int KP, bool LN = false>
-__global__ void __launch_bounds__(kRkThreads) 
-__attribute__((amdgpu_waves_per_eu(E::bytes == 4 || LN ? 2 : 4)))
+__global__ void __launch_bounds__(kRkThreads)
+__attribute__((amdgpu_waves_per_eu(rk_waves<E, PROJ, KP, LN>())))
 block_gemm_rk_kernel(BlockArgs a)
 {
     constexpr bool BF = E::bytes == 2;
@@ -667,8 +729,13 @@ block_gemm_rk_kernel(BlockArgs a)
                 wr[j][h] = src[(idx < kPieces ? idx : kPieces - 1) * WPP + h];
         }
     };
-    auto wstash = [&](int buf) {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(wbuf(buf));
+    // fp32: the last tile (of even, of odd ones) with a value that is not finite
+    __shared__ int inftile[2];
+    if (!BF && tid < 2)
+        inftile[tid] = -1;
+    auto wstash = [&](int it) {
+        u32x4 *dst = reinterpret_cast<u32x4 *>(wbuf(it & 1));
+        u16x2 top = {0, 0};
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int idx = tid + j * kRkThreads;
@@ -682,10 +749,12 @@ block_gemm_rk_kernel(BlockArgs a)
                         x[e] = __uint_as_float(wr[j][e / 4][e % 4]);
                     const int n = idx / (KP / 8), kp = idx - n * (KP / 8);
                     bf8 *d = reinterpret_cast<bf8 *>(dst) + n * (L::PH / 8) + kp;
-                    split3_bf16(x, d[0], d[L::plane / 4], d[2 * (L::plane / 4)]);
+                    split3_bf16(x, d[0], d[L::plane / 4], d[2 * (L::plane / 4)], top);
                 }
             }
         }
+        if (!BF && not_finite(top))
+            inftile[it & 1] = it;
     };
     // Workgroups start at different column tiles, so that at any moment they
     // read different tiles of W instead of all hitting the same L2 lines.
@@ -706,6 +775,7 @@ block_gemm_rk_kernel(BlockArgs a)
         bz[j] = a.bias ? ld<E>(a.bias, nc) : 0.f;
     }
     bf8 ab[L::NP][KQ / 8];
+    u16x2 atop = {0, 0};
     const uint32_t *asrc = static_cast<const uint32_t *>(a.a);
     uint32_t *adst = reinterpret_cast<uint32_t *>(astage);
 #pragma unroll
@@ -747,11 +817,12 @@ block_gemm_rk_kernel(BlockArgs a)
                     const f4 lo = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s);
                     const f4 hi = *reinterpret_cast<const f4 *>(arow + g * KQ + 8 * s + 4);
                     const float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                    split3_bf16(x, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s]);
+                    split3_bf16(x, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s], atop);
                 }
             }
         }
     }
+    const bool rowsinf = !BF && __builtin_amdgcn_ballot_w64(not_finite(atop)) != 0;
     if constexpr (LN) {
         static_assert(BF, "LayerNorm in the prologue: bf16");
         // The rows stay packed between the three passes over them: without
@@ -852,12 +923,16 @@ block_gemm_rk_kernel(BlockArgs a)
         f4 acc[NQ];
         const uint16_t *h = reinterpret_cast<const uint16_t *>(wt);
         tile_product<L, KQ / 8>(ab, h + c * L::PH + g * KQ, 8, acc);
+        if constexpr (!BF) {
+            if (rowsinf || __builtin_amdgcn_readfirstlane(inftile[it & 1]) == it)   // uniform
+                tile_product_f32<L, KQ / 8>(ab, h + c * L::PH + g * KQ, 8, acc);
+        }
         // The next tile goes to the idle buffer before this tile's stores are
         // issued: the wait for its loads counts every earlier vector memory
         // operation, stores included, so stashing after the stores would
         // wait for their completion on every tile.
         if (more) {
-            wstash((it + 1) & 1);
+            wstash(it + 1);
             cfill(phys(it + 1), (it + 1) & 1);
         }
         // Epilogue: lane (g, c) holds rows 4g + i of the wave's 16, column c of tile q;
@@ -999,7 +1074,11 @@ block_gemm_rw_kernel(BlockArgs a)
             }
         }
     };
+    __shared__ int winf;   // fp32: this block's columns of W hold a value that is not finite
+    if (!BF && tid == 0)
+        winf = 0;
     auto wstash = [&](int j0) {
+        u16x2 top = {0, 0};
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int j = j0 + tid + u * T;
@@ -1014,10 +1093,12 @@ block_gemm_rw_kernel(BlockArgs a)
                     const int cj = j / (KP / 8), kp = j % (KP / 8);
                     bf8 *d = reinterpret_cast<bf8 *>(wbase + (cj / L::CT) * L::tile) +
                              (cj % L::CT) * (L::PH / 8) + kp;
-                    split3_bf16(f, d[0], d[L::plane / 4], d[2 * (L::plane / 4)]);
+                    split3_bf16(f, d[0], d[L::plane / 4], d[2 * (L::plane / 4)], top);
                 }
             }
         }
+        if (!BF && not_finite(top))
+            winf = 1;
     };
     wfetch(0);
     for (int k = tid; k < KP; k += T) {
@@ -1049,8 +1130,8 @@ block_gemm_rw_kernel(BlockArgs a)
     int rt = rb * (T / 64) + wv;
     rows4(rt);   // clamped past the last row
     int sub = 0;   // which of the four tiles of rows4 is current
-    if (PROJ || !pairs)
-        __syncthreads();   // colofs
+    if (PROJ || !BF)
+        __syncthreads();   // colofs, winf
     fetch(__shfl(inoff, c, 64), raw);
     wstash(0);
     for (int j0 = kBatch * T; j0 < units; j0 += kBatch * T) {
@@ -1058,6 +1139,7 @@ block_gemm_rw_kernel(BlockArgs a)
         wstash(j0);
     }
     __syncthreads();
+    const bool colsinf = !BF && __builtin_amdgcn_readfirstlane(winf) != 0;
     for (; rt < ntiles; rt += stride) {
         // output offsets of rows 4g + i, then the next tile's rows
         uint32_t rowoff[4];
@@ -1069,6 +1151,7 @@ block_gemm_rw_kernel(BlockArgs a)
         }
         // operands of this tile, zero from C on
         bf8 ab[L::NP][KS];
+        u16x2 atop = {0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int k0 = 32 * s + 8 * g;
@@ -1086,9 +1169,10 @@ block_gemm_rw_kernel(BlockArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     f[e] = __uint_as_float(raw[s][e]);
-                split3_bf16(f, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s]);
+                split3_bf16(f, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s], atop);
             }
         }
+        const bool inf = !BF && (colsinf || __builtin_amdgcn_ballot_w64(not_finite(atop)) != 0);
         if (++sub == 4) {   // uniform
             sub = 0;
             rows4(rt + stride);
@@ -1146,6 +1230,10 @@ block_gemm_rw_kernel(BlockArgs a)
             const uint16_t *h = reinterpret_cast<const uint16_t *>(wbase + ct * L::tile);
             f4 acc[NQ];
             tile_product<L, KS>(ab, h + c * L::PH + 8 * g, 32, acc);
+            if constexpr (!BF) {
+                if (inf)   // uniform
+                    tile_product_f32<L, KS>(ab, h + c * L::PH + 8 * g, 32, acc);
+            }
             store_tile<E, L>(a, acc, (t0 + ct) * L::CT, c, rowoff, rowok, colbias + ct * L::CT,
                              coltab + ct * L::CT);
         }

@@ -645,15 +645,6 @@ __device__ inline void split3_prob(const f4 &a, const f4 &b, bf8 &h, bf8 &m, bf8
     l = as_bf8(lw);
 }
 
-__device__ inline bool all_finite(const float (&x)[8])
-{
-    float m = 0.f;   // x - x is 0 for finite values, NaN otherwise
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        m += x[e] - x[e];
-    return m == 0.f;
-}
-
 template <int D, int QT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict__ k,
@@ -703,16 +694,17 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
             unsigned char *bb = xsm + buf * X::bytes;
             uint16_t *ks = reinterpret_cast<uint16_t *>(bb) + skey * kXKP + 8 * sg;
             uint16_t *vt = reinterpret_cast<uint16_t *>(bb) + 3 * X::kplane;
-            // a buffer's flag names the last block in it with such a value
-            if (!all_finite(kst) || !all_finite(vst))
-                *reinterpret_cast<int *>(bb + X::flag) = blk;
+            u16x2 top = {0, 0};
 #pragma unroll
             for (int x = 0; x < 8; ++x)
                 kst[x] = slot_valid<D>(sg, x) ? kst[x] : 0.f;
             split3_bf16(kst, *reinterpret_cast<bf8 *>(ks), *reinterpret_cast<bf8 *>(ks + X::kplane),
-                        *reinterpret_cast<bf8 *>(ks + 2 * X::kplane));
+                        *reinterpret_cast<bf8 *>(ks + 2 * X::kplane), top);
             bf8 t[3];
-            split3_bf16(vst, t[0], t[1], t[2]);
+            split3_bf16(vst, t[0], t[1], t[2], top);
+            // a buffer's flag names the last block in it with such a value
+            if (not_finite(top))
+                *reinterpret_cast<int *>(bb + X::flag) = blk;
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
                 const U16B u = __builtin_bit_cast(U16B, t[p]);
@@ -726,15 +718,14 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
     };
 
     bf8 qf[QT][3];
-    bool qfin = true;
+    u16x2 qtop = {0, 0};
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
         float x[8];
         load_chunk8<F32, D>(qu + int64_t(q0 + 16 * t + c) * D, g, x);
-        qfin = qfin && all_finite(x);
-        split3_bf16(x, qf[t][0], qf[t][1], qf[t][2]);
+        split3_bf16(x, qf[t][0], qf[t][1], qf[t][2], qtop);
     }
-    const bool qbad = __builtin_amdgcn_ballot_w64(!qfin) != 0;
+    const bool qbad = __builtin_amdgcn_ballot_w64(not_finite(qtop)) != 0;
     f4 OT[QT][NCT];
     float mref[QT], lsum[QT];
 #pragma unroll

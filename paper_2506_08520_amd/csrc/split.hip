@@ -239,7 +239,6 @@ split_keys_kernel(const typename E::T *__restrict__ k, const typename E::T *__re
     // issue.
     // bf16 V is held as pairs of rows (4g, 4g+1) and (4g+2, 4g+3) of one
     // column, the two 16-bit loads landing in the halves of one register.
-    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
     float kr[2][8], vr[2][NCT][4], krn[2][8], vrn[2][NCT][4];
     bf8 kw[2], kwn[2];
     uint32_t vh[2][NCT][2], vhn[2][NCT][2];

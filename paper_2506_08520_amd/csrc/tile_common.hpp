@@ -122,33 +122,80 @@ __device__ inline void split_bf16(const float (&x)[8], bf8 &hi, bf8 &lo)
     lo = __builtin_bit_cast(bf8, l);
 }
 
-// Eight fp32 values as three bf16 terms, x = h + m + l with |l - (x - h - m)|
-// below 2^-24 |x|: h is x truncated to bf16 (never rounded up to infinity), m
-// and l are rounded to nearest even.  Six of the nine products of two such
-// sums (hh, hm, mh, mm, hl, lh) carry a product to fp32 accuracy; they run as
-// one bf16 matrix instruction each, 96 cycles per 16x16x32 tile against 256 of
-// the fp32 matrix instruction.  An infinity keeps m = l = 0; NaN stays NaN.
-__device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l)
+// Eight fp32 values as three bf16 terms, x = h + m + l: h is x truncated to bf16
+// (never rounded up to infinity), m and l are rounded to nearest even.  |m| is below
+// 2^-7 |x| and |l| up to 2^-16 |x|; the sum is exact down to |x| = 2^-110, where l
+// leaves the normal numbers.  Six of the nine products of two such sums (hh, hm, mh,
+// mm, hl, lh) make a product: those left out (ml, lm, ll) reach 2^-22 of it, with
+// either sign and 2^-24.5 of it in the mean square.  They run as one bf16 matrix
+// instruction each, 96 cycles per 16x16x32 tile against 256 of the fp32 matrix
+// instruction.  An infinity or NaN keeps m = l = 0 (found by one test of the eight
+// upper halves).  Its products with the other side's zero
+// terms are NaN all the same: `top` keeps the largest magnitudes (upper halves) of
+// what was split, and where not_finite(top) a tile takes the fp32 matrix instruction
+// (join3_bf16, mfma_f32x8).
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ inline bool not_finite(u16x2 top) { return top.x >= 0x7f80 || top.y >= 0x7f80; }
+
+__device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l, u16x2 &top)
 {
     const NegSel s = neg_selectors();
     U16B hw, mw, lw;
+    float r[8];
+    u16x2 own = {0, 0};
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        float r[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const float v = x[2 * p + e];
-            const float t = __uint_as_float(__float_as_uint(v) & 0xffff0000u);
-            r[e] = fabsf(v) == INFINITY ? 0.f : v - t;
-        }
         hw.w[p] = __builtin_amdgcn_perm(__float_as_uint(x[2 * p + 1]), __float_as_uint(x[2 * p]),
                                         0x07060302u);
-        mw.w[p] = cvt_bf16x2(r[0], r[1]);
-        lw.w[p] = residual_bf16x2(mw.w[p], r[0], r[1], s);
+        own = __builtin_elementwise_max(own, __builtin_bit_cast(u16x2, hw.w[p] & 0x7fff7fffu));
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        r[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
+    if (__builtin_expect(not_finite(own), 0)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (!(fabsf(x[e]) < INFINITY))
+                r[e] = 0.f;
+            if (x[e] != x[e])   // a NaN whose upper half alone would be an infinity
+                hw.w[e / 2] |= e & 1 ? 0x400000u : 0x40u;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        mw.w[p] = cvt_bf16x2(r[2 * p], r[2 * p + 1]);
+        lw.w[p] = residual_bf16x2(mw.w[p], r[2 * p], r[2 * p + 1], s);
+    }
+    top = __builtin_elementwise_max(top, own);
     h = __builtin_bit_cast(bf8, hw);
     m = __builtin_bit_cast(bf8, mw);
     l = __builtin_bit_cast(bf8, lw);
+}
+
+// The values that split3_bf16 took apart.
+__device__ inline void join3_bf16(bf8 h, bf8 m, bf8 l, float (&x)[8])
+{
+    const U16B hw = __builtin_bit_cast(U16B, h), mw = __builtin_bit_cast(U16B, m);
+    const U16B lw = __builtin_bit_cast(U16B, l);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        x[2 * p] = (__uint_as_float(hw.w[p] << 16) + __uint_as_float(mw.w[p] << 16)) +
+                   __uint_as_float(lw.w[p] << 16);
+        x[2 * p + 1] = (__uint_as_float(hw.w[p] & 0xffff0000u) +
+                        __uint_as_float(mw.w[p] & 0xffff0000u)) +
+                       __uint_as_float(lw.w[p] & 0xffff0000u);
+    }
+}
+
+// acc + A B over 32 of the contraction on the fp32 matrix cores, operands in the slots
+// of the bf16 instruction (lane group g: eight k, the same ones on both sides).
+__device__ inline f4 mfma_f32x8(const float (&a)[8], const float (&b)[8], f4 acc)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        acc = mfma4(a[e], b[e], acc);
+    return acc;
 }
 
 // acc + A B over 32 of the contraction, both as three terms, small products first.

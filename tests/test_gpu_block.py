@@ -181,3 +181,41 @@ def test_block_past_256_channels(case, dtype):
                            dtype=dtype, round_output=False)
     got = run_block(inputs, heads, w, s, m, dtype, "nystrom")
     check(got, ref, dtype, f"block {case} {dtype}", beyond_bar=BLOCK_BEYOND_BF16)
+
+
+# Few rows (the weight-resident GEMM), many (the row-resident one at every padded
+# width; 129 to 192 channels stay weight-resident), and the wide GEMM.
+@pytest.mark.parametrize("H,C,heads", [(16, 24, 3), (16, 60, 3), (16, 90, 3), (16, 180, 6),
+                                       (16, 240, 8), (16, 264, 11), (128, 32, 1), (128, 64, 2),
+                                       (128, 96, 6), (128, 180, 6), (128, 240, 8)])
+def test_block_infinities(H, C, heads):
+    """fp32: an infinity in a weight, in the attention's output or in X gives what the
+    float64 evaluation gives (infinities of the same sign, NaN where it has NaN) and
+    leaves every other element alone."""
+    x, wq, bq, wp, bp = W.block_inputs(1, H, H, C, seed=H + C, dtype="f32")
+    x[..., C // 3] = np.abs(x[..., C // 3]) + 0.5
+
+    def both(x, wq, wp):
+        with np.errstate(invalid="ignore"):
+            ref = OB.block_forward(x, wq, bq, wp, bp, heads=heads, window=8, shift=4,
+                                   attention="exact")
+        return run_block((x, wq, bq, wp, bp), heads, 8, 4, 16, "f32", "exact"), ref
+
+    def same(got, ref, what):
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), f"{what}: {np.isnan(got).sum()} NaN"
+        inf = np.isinf(ref)
+        assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], ref[inf]), what
+        ok = np.isfinite(ref)
+        assert np.abs(got[ok] - ref[ok]).max(initial=0.0) <= TOL["f32"], what
+        return inf
+
+    bad = wp.copy()
+    bad[C // 2, C - 1], bad[C // 2, 1] = -np.inf, np.inf
+    inf = same(*both(x, wq, bad), "W_proj")
+    assert inf[..., [1, C - 1]].all() and inf.sum() == 2 * inf[..., 0].size
+    bad = wq.copy()
+    bad[C // 3, 2 * C + 5] = np.inf     # X > 0 there: a column of V and of O
+    assert same(*both(x, bad, wp), "W_qkv, O").all()
+    bad = x.copy()
+    bad[0, 9, 10, 3] = -np.inf          # NaN in its window's outputs only
+    same(*both(bad, wq, wp), "X")
