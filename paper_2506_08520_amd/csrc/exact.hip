@@ -612,10 +612,13 @@ exact_blocked_f32_kernel(const float *__restrict__ q, const float *__restrict__ 
 // about even between the matrix instructions and the vector arithmetic of the
 // exponentials and their split.
 // Splitting an infinity would make NaN of its products with the (often zero)
-// lower terms of the other operand, so a block of keys that holds a value that is
-// not finite -- the staging threads flag it -- and every block of a query tile
-// group that does, takes the fp32 matrix cores.
-// 6144 units of 256 tokens, d_h = 30: 453 -> 361 us; error against 64 bits 3.2e-7 ->
+// lower terms of the other operand, so 32 keys that hold a value that is
+// not finite -- the staging threads flag them -- and every key of a query tile
+// group that does, take the fp32 matrix cores, their operands put together from the
+// terms in LDS.  With one -inf key in 64, 6144 units of 256 tokens 486 us (every
+// block on the fp32 matrix cores 452; reading the operands from memory again 697),
+// 384 units of 1024 tokens 435 us (451; 593).
+// 6144 units of 256 tokens, d_h = 30: 453 -> 360 us; error against 64 bits 3.2e-7 ->
 // 2.5e-7.  Two query tiles per wave (four waves per SIMD instead of two) measured
 // the same where they fit the registers (d_h = 16: 284 us against 287).
 
@@ -673,8 +676,8 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
             vt[(D + r / kXB) * kXVP + r % kXB] = uint16_t(0);
         }
     }
-    if (threadIdx.x < 2)
-        *reinterpret_cast<int *>(xsm + threadIdx.x * X::bytes + X::flag) = -1;
+    if (threadIdx.x < 4)
+        reinterpret_cast<int *>(xsm + (threadIdx.x >> 1) * X::bytes + X::flag)[threadIdx.x & 1] = -1;
     __syncthreads();
     // Staging: thread t of the first 256 takes key t / 4, chunk t % 4.
     const bool stager = threadIdx.x < 256;
@@ -702,9 +705,9 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
                         *reinterpret_cast<bf8 *>(ks + 2 * X::kplane), top);
             bf8 t[3];
             split3_bf16(vst, t[0], t[1], t[2], top);
-            // a buffer's flag names the last block in it with such a value
+            // a flag of a buffer (one per 32 keys) names the last block with such a value
             if (not_finite(top))
-                *reinterpret_cast<int *>(bb + X::flag) = blk;
+                reinterpret_cast<int *>(bb + X::flag)[skey >> 5] = blk;
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
                 const U16B u = __builtin_bit_cast(U16B, t[p]);
@@ -759,21 +762,36 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
             fetch(blk + 1);
         const unsigned char *bb = xsm + buf * X::bytes;
         const uint16_t *ks = reinterpret_cast<const uint16_t *>(bb), *vt = ks + 3 * X::kplane;
-        const bool bad = qbad || __builtin_amdgcn_readfirstlane(
-                                     *reinterpret_cast<const int *>(bb + X::flag)) == blk;
-        if (!bad) {   // uniform
 #pragma unroll 1
-            for (int kp = 0; kp < 2; ++kp) {   // 32 keys
+        for (int kp = 0; kp < 2; ++kp) {   // 32 keys
+            f4 st[QT][2];   // S^T[key 32kp+16h+4g+i][query q0+16t+c]
+            // Softmax of query tile t over st, and its probabilities.
+            auto probs = [&](int t) {
+                raise(t, fmaxf(fmaxf(fmaxf(st[t][0][0], st[t][0][1]),
+                                     fmaxf(st[t][0][2], st[t][0][3])),
+                               fmaxf(fmaxf(st[t][1][0], st[t][1][1]),
+                                     fmaxf(st[t][1][2], st[t][1][3]))));
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        st[t][h][i] = fast_exp2(fmaf(s2, st[t][h][i], -mref[t]));
+                        lsum[t] += st[t][h][i];
+                    }
+            };
+            const uint16_t *krow = ks + (32 * kp + c) * kXKP + 8 * g;
+            const uint16_t *vrow = vt + c * kXVP + 32 * kp + 8 * g;
+            if (!qbad && __builtin_amdgcn_readfirstlane(
+                             reinterpret_cast<const int *>(bb + X::flag)[kp]) != blk) {   // uniform
                 // K's terms are dead before V's are read (registers): the
                 // scores of every query tile first.
                 bf8 kv[2][3];
-                f4 st[QT][2];   // S^T[key 32kp+16h+4g+i][query q0+16t+c]
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int p = 0; p < 3; ++p)
-                        kv[h][p] = *reinterpret_cast<const bf8 *>(
-                            ks + p * X::kplane + (32 * kp + 16 * h + c) * kXKP + 8 * g);
+                        kv[h][p] = *reinterpret_cast<const bf8 *>(krow + p * X::kplane +
+                                                                  16 * h * kXKP);
 #pragma unroll
                 for (int t = 0; t < QT; ++t)
 #pragma unroll
@@ -786,21 +804,11 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
                 for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
                     for (int p = 0; p < 3; ++p)
-                        vf[ct][p] = *reinterpret_cast<const bf8 *>(
-                            vt + p * X::vplane + (16 * ct + c) * kXVP + 32 * kp + 8 * g);
+                        vf[ct][p] = *reinterpret_cast<const bf8 *>(vrow + p * X::vplane +
+                                                                   16 * ct * kXVP);
 #pragma unroll
                 for (int t = 0; t < QT; ++t) {
-                    raise(t, fmaxf(fmaxf(fmaxf(st[t][0][0], st[t][0][1]),
-                                         fmaxf(st[t][0][2], st[t][0][3])),
-                                   fmaxf(fmaxf(st[t][1][0], st[t][1][1]),
-                                         fmaxf(st[t][1][2], st[t][1][3]))));
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            st[t][h][i] = fast_exp2(fmaf(s2, st[t][h][i], -mref[t]));
-                            lsum[t] += st[t][h][i];
-                        }
+                    probs(t);
                     bf8 ph, pm, pl;
                     split3_prob(st[t][0], st[t][1], ph, pm, pl);
 #pragma unroll
@@ -808,38 +816,50 @@ exact_blocked_split_kernel(const float *__restrict__ q, const float *__restrict_
                         OT[t][ct] = mfma_split3(vf[ct][0], vf[ct][1], vf[ct][2], ph, pm, pl,
                                                 OT[t][ct]);
                 }
-            }
-        } else {
-            for (int kt = 0; kt < 4; ++kt) {
-                const int key0 = blk * kXB + 16 * kt;
-                float kf[8];   // K row key0 + c, slots of group g
-                load_chunk8<F32, D>(ku + int64_t(key0 + c) * D, g, kf);
-                f4 vl[NCT];    // V[key0 + 4g + i][16ct + c]
+            } else {
+                auto join = [](const uint16_t *x, int plane, float (&y)[8]) {
+                    join3_bf16(*reinterpret_cast<const bf8 *>(x),
+                               *reinterpret_cast<const bf8 *>(x + plane),
+                               *reinterpret_cast<const bf8 *>(x + 2 * plane), y);
+                };
+                float kf[2][8];
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int f = 16 * ct + c;
-                        const float x = vu[int64_t(key0 + 4 * g + i) * D + (f < D ? f : D - 1)];
-                        vl[ct][i] = f < D ? x : 0.f;
-                    }
+                for (int h = 0; h < 2; ++h)
+                    join(krow + 16 * h * kXKP, X::kplane, kf[h]);
 #pragma unroll
                 for (int t = 0; t < QT; ++t) {
-                    float x[8];
-                    load_chunk8<F32, D>(qu + int64_t(q0 + 16 * t + c) * D, g, x);
-                    f4 st = {0.f, 0.f, 0.f, 0.f};
+                    bf8 qt[3];   // joined here: not kept in registers over the blocks
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        st = mfma4(kf[e], x[e], st);
-                    raise(t, fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])));
+                    for (int p = 0; p < 3; ++p) {
+                        qt[p] = qf[t][p];
+                        asm volatile("" : "+v"(qt[p]));
+                    }
+                    float x[8];
+                    join3_bf16(qt[0], qt[1], qt[2], x);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        st[t][h] = mfma_f32x8(kf[h], x, f4{0.f, 0.f, 0.f, 0.f});
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                f4 vl[NCT][2];   // V[key 32kp+16h+4g+i][16ct+c]
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    float y[8];
+                    join(vrow + 16 * ct * kXVP, X::vplane, y);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        st[i] = fast_exp2(fmaf(s2, st[i], -mref[t]));
-                        lsum[t] += st[i];
+                        vl[ct][0][i] = y[i];
+                        vl[ct][1][i] = y[4 + i];
                     }
+                }
+#pragma unroll
+                for (int t = 0; t < QT; ++t) {
+                    probs(t);
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct)
-                        OT[t][ct] = mm16_acc(vl[ct], st, OT[t][ct]);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            OT[t][ct] = mm16_acc(vl[ct][h], st[t][h], OT[t][ct]);
                 }
             }
         }

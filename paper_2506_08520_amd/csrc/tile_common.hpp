@@ -173,18 +173,20 @@ __device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l, 
     l = __builtin_bit_cast(bf8, lw);
 }
 
-// The values that split3_bf16 took apart.
+// The values that split3_bf16 took apart (join3: terms as the upper halves of words).
+__device__ inline float join3(uint32_t h, uint32_t m, uint32_t l)
+{
+    return (__uint_as_float(h) + __uint_as_float(m)) + __uint_as_float(l);
+}
+
 __device__ inline void join3_bf16(bf8 h, bf8 m, bf8 l, float (&x)[8])
 {
     const U16B hw = __builtin_bit_cast(U16B, h), mw = __builtin_bit_cast(U16B, m);
     const U16B lw = __builtin_bit_cast(U16B, l);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        x[2 * p] = (__uint_as_float(hw.w[p] << 16) + __uint_as_float(mw.w[p] << 16)) +
-                   __uint_as_float(lw.w[p] << 16);
-        x[2 * p + 1] = (__uint_as_float(hw.w[p] & 0xffff0000u) +
-                        __uint_as_float(mw.w[p] & 0xffff0000u)) +
-                       __uint_as_float(lw.w[p] & 0xffff0000u);
+        x[2 * p] = join3(hw.w[p] << 16, mw.w[p] << 16, lw.w[p] << 16);
+        x[2 * p + 1] = join3(hw.w[p] & 0xffff0000u, mw.w[p] & 0xffff0000u, lw.w[p] & 0xffff0000u);
     }
 }
 
