@@ -140,6 +140,12 @@ __global__ void __launch_bounds__(256) block_gemm_kernel(BlockArgs a)
                 }
             }
         } else {
+            // The chunk is summed by itself: a sum over C is two short chains of
+            // roundings, not one.
+            f4 part[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                part[i][0] = part[i][1] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < kBK / 4; ++s) {
                 float av[2], bv[2];
@@ -152,8 +158,13 @@ __global__ void __launch_bounds__(256) block_gemm_kernel(BlockArgs a)
                 for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
                     for (int tj = 0; tj < 2; ++tj)
-                        acc[ti][tj] = mfma4(av[ti], bv[tj], acc[ti][tj]);
+                        part[ti][tj] = mfma4(av[ti], bv[tj], part[ti][tj]);
             }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] += part[i][j];
         }
         __syncthreads();
         if (more) {
@@ -1354,7 +1365,13 @@ void launch_gemm(const BlockArgs &a, hipStream_t stream)
 {
     if (try_rk<E, PROJ>(a, stream))
         return;
-    if (wide_ok(a, PROJ)) {
+    // fp32 with no more 64 x 64 tiles than compute units: those are done in one go,
+    // and a 128 x 128 tile takes longer than one of them.  Whole blocks, wide kernel
+    // -> this rule: C = 264, 1024 rows (208 tiles of the QKV product) 62 -> 49 us, C = 1024,
+    // 256 rows (192) 179 -> 161 us; C = 384, 1024 rows (288) 77 us with the wide kernel, 92
+    // without.  (bf16: the wide kernel is faster at every size.)
+    const bool few = E::bytes == 4 && a.rtiles * a.ctiles <= 256;
+    if (!few && wide_ok(a, PROJ)) {
         using F = WideCfg<E>;
         BlockArgs b = a;
         b.rtiles = int((a.rows + F::BM - 1) / F::BM);
