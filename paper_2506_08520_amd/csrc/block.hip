@@ -1361,10 +1361,14 @@ bool try_rk(const BlockArgs &a, hipStream_t stream)
 }
 
 template <class E, bool PROJ>
-void launch_gemm(const BlockArgs &a, hipStream_t stream)
+hipError_t launch_gemm(const BlockArgs &a, hipStream_t stream)
 {
     if (try_rk<E, PROJ>(a, stream))
-        return;
+        return hipGetLastError();
+    // The kernels below have no LayerNorm.  layer_supported() and the plan of the
+    // workspace keep every layer on the path above.
+    if (a.lnw)
+        return hipErrorInvalidValue;
     // fp32 with no more 64 x 64 tiles than compute units: those are done in one go,
     // and a 128 x 128 tile takes longer than one of them.  Whole blocks, wide kernel
     // -> this rule: C = 264, 1024 rows (208 tiles of the QKV product) 62 -> 49 us, C = 1024,
@@ -1378,10 +1382,11 @@ void launch_gemm(const BlockArgs &a, hipStream_t stream)
         b.ctiles = (a.ncols + F::BN - 1) / F::BN;
         hipLaunchKernelGGL((block_gemm_wide_kernel<E, PROJ>),
                            dim3(unsigned(b.rtiles) * unsigned(b.ctiles)), dim3(256), 0, stream, b);
-        return;
+        return hipGetLastError();
     }
     const unsigned blocks = unsigned(a.rtiles) * unsigned(a.ctiles);
     hipLaunchKernelGGL((block_gemm_kernel<E, PROJ>), dim3(blocks), dim3(256), 0, stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1490,10 +1495,8 @@ hipError_t launch_block_gemm(const BlockGemm &g, hipStream_t stream)
     a.lnb = g.lnb;
     a.eps = g.eps;
     if (g.dtype == 0)
-        g.proj ? launch_gemm<F32, true>(a, stream) : launch_gemm<F32, false>(a, stream);
-    else
-        g.proj ? launch_gemm<BF16, true>(a, stream) : launch_gemm<BF16, false>(a, stream);
-    return hipGetLastError();
+        return g.proj ? launch_gemm<F32, true>(a, stream) : launch_gemm<F32, false>(a, stream);
+    return g.proj ? launch_gemm<BF16, true>(a, stream) : launch_gemm<BF16, false>(a, stream);
 }
 
 }  // namespace nystra
