@@ -622,13 +622,13 @@ __device__ inline void store_tile(const BlockArgs &a, const f4 (&acc)[L::CT / 16
     constexpr bool BF = E::bytes == 2;
     typename E::T *dst = static_cast<typename E::T *>(a.out0);
     const bool odd = c & 1;
+    if (a.pair) {   // uniform
 #pragma unroll
-    for (int q = 0; q < L::CT / 16; ++q) {
-        const int j = 16 * q + c;
-        if (n0 + j >= a.ncols)   // column pairs lie on one side of ncols
-            continue;
-        const float b = bias[j];
-        if (a.pair) {
+        for (int q = 0; q < L::CT / 16; ++q) {
+            const int j = 16 * q + c;
+            if (n0 + j >= a.ncols)   // column pairs lie on one side of ncols
+                continue;
+            const float b = bias[j];
             const uint32_t col = coltab[j & ~1];
 #pragma unroll
             for (int pp = 0; pp < 2; ++pp) {
@@ -644,7 +644,14 @@ __device__ inline void store_tile(const BlockArgs &a, const f4 (&acc)[L::CT / 16
                         *reinterpret_cast<float2 *>(dst + (ro + col)) = make_float2(lo, hi);
                 }
             }
-        } else {
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < L::CT / 16; ++q) {
+            const int j = 16 * q + c;
+            if (n0 + j >= a.ncols)
+                continue;
+            const float b = bias[j];
             const uint32_t col = coltab[j];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -685,12 +692,13 @@ block_gemm_rk_kernel(BlockArgs a)
     // ---- A: the workgroup's 128 rows are staged in LDS, SR at a time, with
     // coalesced 4-byte loads (lanes take consecutive words of a row; bf16 words
     // hold two elements), then each lane copies its operand slots -- rows
-    // 16 wv + c, k = g KQ + s -- into registers.  The stage and its
-    // offset tables share LDS with the W tiles.
+    // 16 wv + c, k = g KQ + s -- into registers.  The stage shares LDS with the W
+    // tiles; its offset tables have their own (in the stage's array they would be
+    // read again after every store to it: 0.7 us of 12 at 25600 rows, C = 180).
     constexpr int EPW = BF ? 2 : 1;              // elements per 4-byte word
     constexpr int AWL = L::AWL, AP = L::AP;
-    int *rowbase = reinterpret_cast<int *>(lds_all + L::rowbase);   // row r's element offset (-1: none)
-    int *colofs = reinterpret_cast<int *>(lds_all + L::colofs);     // word w's offset in a row
+    __shared__ int rowbase[kRkRows];   // row r's element offset (-1: none)
+    __shared__ int colofs[AWL];        // word w's offset in a row
     float *astage = lds_all;
     if (tid < kRkRows) {
         const int64_t row = m0 + tid;
@@ -946,12 +954,6 @@ block_gemm_rk_kernel(BlockArgs a)
             wstash(it + 1);
             cfill(phys(it + 1), (it + 1) & 1);
         }
-        // Epilogue: lane (g, c) holds rows 4g + i of the wave's 16, column c of tile q;
-        // destination = row part (per lane, computed once) + column part (table).
-        // With a.pair, lanes c and c ^ 1 swap one value per two rows so that the
-        // even lane holds columns (c, c + 1) of row 4g + 2p and the odd lane
-        // those of row 4g + 2p + 1: one 4-byte (bf16) or 8-byte (fp32) store per
-        // two outputs.  Pairs never straddle a head or Q/K/V (d_h and C even).
         store_tile<E, L>(a, acc, L::CT * ct, c, rowoff, rowok, colbias + L::CT * ct, coltab[it & 1]);
         __syncthreads();
     }
@@ -1294,12 +1296,14 @@ void launch_rk_ln(BlockArgs &a, hipStream_t stream)
     // 88 against 131.  fp32 from 129 to 192 channels is the exception at any size
     // (82944 rows, C = 180: 290 -> 257 us): 128 columns a group fit there, and the
     // row-resident kernel has one workgroup's registers per CU to hide latency.
-    if (blocks < 128 || (E::bytes == 4 && KP == 192)) {
-        launch_rw_ln<E, PROJ, KP, LN>(a, stream);
-        return;
+    if constexpr (!(E::bytes == 4 && KP == 192)) {
+        if (blocks >= 128) {
+            hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, LN>), dim3(unsigned(blocks)),
+                               dim3(kRkThreads), 0, stream, a);
+            return;
+        }
     }
-    hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, LN>), dim3(unsigned(blocks)),
-                       dim3(kRkThreads), 0, stream, a);
+    launch_rw_ln<E, PROJ, KP, LN>(a, stream);
 }
 
 template <class E, bool PROJ, int KP>

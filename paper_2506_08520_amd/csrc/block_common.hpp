@@ -82,8 +82,7 @@ struct RkLds {
     static constexpr int AWL = KP / (BF ? 2 : 1);             // words per staged row
     // row pitch (words; + 8: fewer bank conflicts than + 4 in the operand reads)
     static constexpr int AP = AWL + 8;
-    static constexpr int rowbase = SR * AP, colofs = rowbase + kRkRows;
-    static constexpr int astage = colofs + AWL;               // the stage and its offset tables
+    static constexpr int astage = SR * AP;
     static constexpr int total = 2 * tile > astage ? 2 * tile : astage;
 };
 

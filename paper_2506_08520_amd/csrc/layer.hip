@@ -90,8 +90,7 @@ layer_tail_kernel(TailArgs a)
 
     // ---- Projection: O's rows staged in LDS with coalesced 4-byte loads, then
     // the operand slots k = g KQ + s of row c into registers.
-    int *rowbase = reinterpret_cast<int *>(lds + R::rowbase);
-    int *colofs = reinterpret_cast<int *>(lds + R::colofs);
+    __shared__ int rowbase[kRkRows], colofs[AWL];   // of row r (-1: none), of word w
     if (tid < kRkRows) {
         const int64_t r = m0 + tid;
         int base = -1;
