@@ -1289,15 +1289,23 @@ void launch_rk_ln(BlockArgs &a, hipStream_t stream)
 {
     const int64_t blocks = (a.rows + kRkRows - 1) / kRkRows;
     // Few rows (fewer row blocks than half the compute units): column groups on
-    // more of the chip.  4096 rows, whole blocks: C = 180 fp32 74 -> 39 us, C = 192
-    // bf16 37 -> 28 us, C = 240 bf16 47 -> 27 us.  With more rows every group's
-    // pass over them costs more than the streaming's waits: 25600 rows, C = 180
-    // bf16 47 us against 48, 65536 rows, C = 240 bf16 104 against 117, C = 96 fp32
-    // 88 against 131.  fp32 from 129 to 192 channels is the exception at any size
-    // (82944 rows, C = 180: 290 -> 257 us): 128 columns a group fit there, and the
-    // row-resident kernel has one workgroup's registers per CU to hide latency.
+    // more of the chip.  With more rows every group's pass over them costs more than
+    // the streaming's waits.  Whole blocks of 8 x 8 windows, row-resident against
+    // weight-resident (us), at 64, 120, 136 and 512 row blocks:
+    //   bf16 C =  64  19.4/17.9  22.4/22.5  23.7/24.3  31.7/34.6
+    //   bf16 C = 180  41.0/29.9  45.9/41.6  46.2/42.6  74.2/75.3
+    //   bf16 C = 256  51.9/39.6  56.4/58.1  58.6/63.0  100/129
+    //   fp32 C =  64  29.3/26.4  34.7/32.0  37.6/39.3  50.2/52.9
+    //   fp32 C = 128  51.2/43.4  55.1/64.4  58.4/69.6  93.5/139
+    //   fp32 C = 256  131/63.0   139/107    144/120    303/332
+    // fp32 from 65 to 128 channels changes sides earlier (80 row blocks: 53.1/54.8,
+    // C = 96 47.1/45.1; 96: 53.4/63.1, 49.1/55.3).  fp32 from 129 to 192 channels is
+    // weight-resident at any size (C = 180: 86.1/67.7 at 96, 185/183 at 512, 259/232 at
+    // 648): 128 columns a group fit there, and the row-resident kernel has one
+    // workgroup's registers per CU to hide latency.
+    constexpr int kFew = E::bytes == 4 && KP == 128 ? 88 : 128;
     if constexpr (!(E::bytes == 4 && KP == 192)) {
-        if (blocks >= 128) {
+        if (blocks >= kFew) {
             hipLaunchKernelGGL((block_gemm_rk_kernel<E, PROJ, KP, LN>), dim3(unsigned(blocks)),
                                dim3(kRkThreads), 0, stream, a);
             return;
