@@ -219,3 +219,47 @@ def test_block_infinities(H, C, heads):
     bad = x.copy()
     bad[0, 9, 10, 3] = -np.inf          # NaN in its window's outputs only
     same(*both(bad, wq, wp), "X")
+
+
+# The kernels of large maps: from 128 row blocks of 128 on (88 in fp32 with 65 to 128
+# channels) the row-resident GEMM, below it the weight-resident one, which with more
+# row tiles than waves walks over several (fp32 of 129 to 192 channels at any size).
+LARGE = [
+    (1, 128, 136, 24, 3, 8, 4, 16),     # padded widths 32 ...
+    (1, 130, 130, 32, 1, 10, 5, 25),    # 16900 rows: a partial row block and row tile
+    (2, 72, 128, 60, 2, 8, 3, 16),      # ... 64
+    (1, 128, 136, 45, 3, 8, 4, 16),     # odd C and d_h (bf16: the 64 x 64 kernel)
+    (1, 133, 126, 96, 6, 7, 3, 7),      # ... 128; 16758 rows
+    (1, 128, 128, 126, 6, 8, 0, 16),    # C % 8 != 0
+    (1, 136, 128, 180, 6, 8, 4, 16),    # ... 192
+    (1, 128, 136, 192, 6, 8, 4, 32),
+    (1, 130, 130, 240, 8, 10, 5, 25),   # ... 256
+    (1, 128, 136, 256, 8, 8, 4, 16),
+    (1, 80, 160, 240, 8, 8, 4, 16),     # 100 row blocks: weight-resident, two tiles a wave
+    (1, 100, 130, 256, 8, 10, 0, 25),
+    (1, 96, 160, 66, 3, 8, 4, 16),      # 120: row-resident in fp32
+    (1, 288, 288, 180, 6, 32, 0, 16),   # fp32: thirteen row tiles a wave
+]
+
+
+def window_sample(x, window, shift, count=6):
+    """The tokens of `count` windows of x as images of one window each, and their
+    flat pixels; the last windows (the last rows of every GEMM) among them."""
+    Bn, H, Wd, C = x.shape
+    idx = OB.window_tokens_roll(Bn, H, Wd, window, shift)
+    pick = np.unique(np.linspace(0, idx.shape[0] - 1, count).round().astype(int))
+    return x.reshape(-1, C)[idx[pick]].reshape(len(pick), window, window, C), idx[pick]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", LARGE, ids=lambda c: "x".join(map(str, c)))
+def test_block_large_maps(case, dtype):
+    Bn, H, Wd, C, heads, w, s, m = case
+    inputs = W.block_inputs(Bn, H, Wd, C, seed=H * Wd + C, dtype=dtype)
+    xs, pixels = window_sample(inputs[0], w, s)
+    ref = OB.block_forward(xs, *inputs[1:], heads=heads, window=w, shift=0, m=m, dtype=dtype,
+                           round_output=False)
+    got = run_block(inputs, heads, w, s, m, dtype, "nystrom")
+    assert np.isfinite(got).all()
+    check(got.reshape(-1, C)[pixels].reshape(ref.shape), ref, dtype, f"block {case} {dtype}",
+          beyond_bar=BLOCK_BEYOND_BF16)

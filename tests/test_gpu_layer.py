@@ -97,6 +97,38 @@ def test_fused_layer(case):
     assert np.abs(n64(y) - ref).max() <= 0.15 * rms
 
 
+# Maps whose QKV product runs on the row-resident kernel (128 row blocks of 128 and
+# more) at each padded width, and on the weight-resident one with two row tiles a wave.
+LARGE = [
+    (1, 128, 136, 28, 2, 8, 4, 16), (1, 130, 130, 32, 1, 10, 5, 25), (1, 128, 136, 60, 2, 8, 0, 16),
+    (1, 133, 126, 96, 6, 7, 3, 7), (2, 72, 128, 128, 4, 8, 4, 16), (1, 128, 136, 180, 6, 8, 4, 16),
+    (1, 130, 130, 240, 8, 10, 5, 25), (1, 128, 128, 256, 8, 8, 4, 32),
+    (1, 80, 160, 240, 8, 8, 4, 16), (1, 100, 130, 256, 8, 10, 0, 25),
+]
+
+
+@pytest.mark.parametrize("case", LARGE, ids=lambda c: "x".join(map(str, c)))
+def test_fused_layer_large_maps(case):
+    """As test_fused_layer, on six windows of the map (the last rows among them)."""
+    Bn, H, Wd, C, heads, w, s, m = case
+    blk = make(C, heads, w, s, m, "nystrom")
+    x = torch.randn(Bn, H, Wd, C, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    assert blk._fusable(x)
+    idx = OB.window_tokens_roll(Bn, H, Wd, w, s)
+    pick = idx[np.unique(np.linspace(0, idx.shape[0] - 1, 6).round().astype(int))]
+    rows = torch.from_numpy(pick).cuda()
+    y, z = blk(x), composed(blk, x)
+    assert torch.isfinite(y).all()
+    blk.attn.shift = 0
+    ref = exact(blk, x.view(-1, C)[rows].view(-1, w, w, C))
+    rms = np.sqrt((ref ** 2).mean())
+    e = {k: np.sqrt(((n64(t.view(-1, C)[rows]).reshape(ref.shape) - ref) ** 2).mean()) / rms
+         for k, t in (("fused", y), ("composed", z))}
+    print(f"layer {case}: rel {e}")
+    assert e["fused"] <= 1.3e-2
+    assert e["fused"] <= 1.1 * e["composed"]
+
+
 def test_no_biases():
     blk = make(64, 2, 8, 4, 16, "nystrom")
     blk.mlp[0].bias = blk.mlp[2].bias = None
@@ -170,6 +202,49 @@ def test_large_values_and_gelu_tails():
     rms = np.sqrt((ref ** 2).mean())
     assert np.sqrt(((n64(y) - ref) ** 2).mean()) <= 1.1 * np.sqrt(((n64(z) - ref) ** 2).mean())
     assert np.isfinite(n64(y)).all() and rms > 0
+
+
+def test_values_that_are_not_finite():
+    """NaN and infinities stay in the windows of their tokens, and in a token's own
+    row where they arise after the attention, as in the composition."""
+    blk = make(64, 2, 8, 4, 16, "exact")
+    x = torch.randn(1, 32, 32, 64, generator=torch.Generator().manual_seed(7)).bfloat16().cuda()
+    x[0, 5, 6, 7], x[0, 21, 30, 0] = float("nan"), float("inf")
+    y, z = blk(x), composed(blk, x)
+    assert torch.equal(torch.isfinite(y), torch.isfinite(z))
+    assert (~torch.isfinite(y)).sum() == 2 * 64 * 64
+    ok = torch.isfinite(z)
+    assert (y[ok].float() - z[ok].float()).abs().max() <= 0.15 * z[ok].float().std()
+    x = x.nan_to_num(nan=0.5, posinf=0.5)
+    blk.mlp[0].bias.data[5] = float("inf")       # GELU(inf) = inf: every value of Y
+    y, z = blk(x), composed(blk, x)
+    assert torch.equal(torch.isnan(y), torch.isnan(z)) and torch.equal(y[torch.isinf(z)], z[torch.isinf(z)])
+    assert torch.isinf(z).any()
+
+
+@pytest.mark.parametrize("C,H", [(64, 16), (180, 128), (320, 16)])
+def test_graph_replays(C, H):
+    """The layer captured in a graph: replays after changes of the input, with the
+    program's own work between them, equal the eager call."""
+    blk = make(C, C // 30 if C == 180 else C // 32, 8, 4, 16, "nystrom")
+    gen = torch.Generator().manual_seed(7)
+    x = torch.randn(1, H, H, C, generator=gen).bfloat16().cuda()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        blk(x)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = blk(x)
+    for _ in range(3):
+        x.copy_(torch.randn(1, H, H, C, generator=gen).bfloat16())
+        want = blk(x).clone()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
 
 
 class _Twice(nn.Linear):
