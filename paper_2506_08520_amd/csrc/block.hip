@@ -9,11 +9,14 @@
 //         the epilogue writes Q, K, V straight into [window][head][N][d_h].
 //   PROJ  A row r = token r's d_h-wide slices of O, one per head (the head
 //         concatenation is a gather); the epilogue writes Y at the pixel.
-// A workgroup computes a 64 x 64 tile of the product over 32-deep chunks of
-// the contraction staged in LDS, the next chunk's loads in flight while the
-// current one is multiplied; four waves each own a 32 x 32 quarter (2 x 2
-// MFMA tiles).  Blocks are mapped so that the column tiles of one row tile
-// run on the same XCD and share its L2 for the gathered rows.
+// Four kernels compute them.  C <= 256 (weights packed beforehand): the row-resident and
+// the weight-resident GEMM, launch_rk_ln() says which.  Above, widths that are
+// multiples of 8: 128 x 128 tiles (wide).  Everything else (odd widths, unaligned
+// tensors, few fp32 rows past 256 channels): block_gemm_kernel, a 64 x 64 tile of the
+// product over 32-deep chunks of the contraction staged in LDS, the next chunk's loads in
+// flight while the current one is multiplied; four waves each own a 32 x 32 quarter (2 x 2
+// MFMA tiles).  Tiles are mapped so that the column tiles of one row tile run on the
+// same XCD and share its L2 for the gathered rows.
 #include <type_traits>
 
 #include "block_common.hpp"

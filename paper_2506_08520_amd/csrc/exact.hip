@@ -440,9 +440,10 @@ exact_blocked_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict_
     }
 }
 
-// ---- fp32, N = 64, 128 or 192: the same blocked structure on the fp32 matrix
-// cores (splitting a key block into bf16 terms, as below, costs more than the few
-// queries that share it gain: N = 64, 6144 units 46 us here, 67 us split).  K rows and V^T are staged as fp32; S^T tiles are eight-step
+// ---- fp32, N = 64 or 128: the same blocked structure on the fp32 matrix cores
+// (splitting a key block into bf16 terms, as below, costs more than the few
+// queries that share it gain: N = 64, 6144 units 46 us here, 67 us split).  K rows
+// and V^T are staged as fp32; S^T tiles are eight-step
 // 16x16x4 products over the feature slots (the slot layout of load_chunk8);
 // the probabilities stay fp32 and feed O^T += V^T P^T directly in the
 // D-layout, with V^T read as the transposed left operand.
@@ -601,7 +602,9 @@ exact_blocked_f32_kernel(const float *__restrict__ q, const float *__restrict__ 
     }
 }
 
-// ---- fp32, N a multiple of 64 from 256 on: the same blocked structure ------------------
+// ---- fp32, N = 256, 320, 384, 448 and the multiples of 512: the same blocked structure --
+// (exact_blocked_ok(): groups of 64 queries that divide evenly into workgroups of
+// four to eight waves; other multiples of 32 run exact_tiled_kernel)
 //
 // Every product runs on the bf16 matrix cores with both operands as three bf16
 // terms (six products, mfma_split3): 96 cycles per 16x16x32 tile against 256 on

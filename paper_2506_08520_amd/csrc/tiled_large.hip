@@ -335,7 +335,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
         }
     };
     // One pair of key tiles for every landmark tile: ones column, logits,
-    // running maxima, G_U^n and T.  The K chunks stay unmasked: their
+    // running maxima, G_U^n and T.  The K chunks stay unmasked (but see RAG): their
     // overlapping slots meet zeros in the Qbar slots.
     auto process = [&](int t0, float (&kr_)[2][8], bf8 (&kw_)[2], float (&vr_)[2][NCT][4],
                        uint32_t (&vh_)[2][NCT][2]) {
@@ -442,7 +442,7 @@ tiled_large_kernel(const typename E::T *__restrict__ q, const typename E::T *__r
                              : RAG && mnew == -INFINITY ? 0.f : a.s2 * mnew;
             if constexpr (BFM) {
                 // bf16 product over the 32 keys of the pair, lane group g
-                // supplying keys 4g..4g+3 of both tiles (N % 32 == 0 here)
+                // supplying keys 4g..4g+3 of both tiles (N % 32 == 0 with BFM)
                 float gk[8];
 #pragma unroll
                 for (int h = 0; h < 2; ++h)

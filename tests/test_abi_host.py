@@ -372,3 +372,50 @@ def test_block_pack_and_packed_forward_validation(L):
     assert f(packed=ws) == EOVERLAP
     assert f(ws=ws + 64) == EWS                  # the other checks are nystra_block_forward's
     assert f(s=bshape(batch=0), packed=None) == OK
+
+
+def test_layer_forward_validation(L):
+    C, hidden = 96, 192
+    s = bshape()
+    need = B.nystra_block_packed_size(C, B.BF16)
+    nb = B.nystra_block_workspace_size(s, 16, B.BF16)
+    at = {n: P + (i << 24) for i, n in enumerate(
+        ("x", "wq", "wp", "pk", "y", "ws", "bq", "bp", "norm1_w", "norm1_b", "norm2_w",
+         "norm2_b", "w1", "b1", "w2", "b2"))}
+
+    def f(s=s, dtype=B.BF16, pb=need, nb=nb, layer=True, eps1=1e-5, eps2=1e-5, hidden=hidden,
+          attention=0, **kw):
+        p = {**at, **kw}
+        lp = B.LayerParams(*(p[n] for n in ("norm1_w", "norm1_b", "norm2_w", "norm2_b", "w1",
+                                            "b1", "w2", "b2")), eps1, eps2, hidden)
+        return L.nystra_layer_forward(p["x"], p["wq"], p["bq"], p["wp"], p["bp"], p["pk"], pb,
+                                      ctypes.byref(lp) if layer else None, p["y"],
+                                      ctypes.byref(s), 16, dtype, None, attention, p["ws"], nb,
+                                      None)
+
+    assert f(layer=False) == ENULL
+    for n in ("x", "wq", "wp", "pk", "y", "norm1_w", "norm1_b", "norm2_w", "norm2_b", "w1", "w2"):
+        assert f(**{n: None}) == ENULL, n
+    assert f(ws=None) == EWS
+    for n in ("x", "y", "w1", "w2"):             # read and written in four-byte pieces
+        assert f(**{n: at[n] + 2}) == EALIGN, n
+    for n in ("wq", "wp", "bq", "bp", "norm1_w", "norm1_b", "norm2_w", "norm2_b", "b1", "b2"):
+        assert f(**{n: at[n] + 1}) == EALIGN, n
+    assert f(pk=at["pk"] + 64) == EALIGN
+    for n in ("x", "wq", "wp", "bq", "bp", "pk", "norm1_w", "norm1_b", "norm2_w", "norm2_b",
+              "w1", "b1", "w2", "b2"):           # each input against Y and the workspace
+        assert f(**{n: at["y"]}) == EOVERLAP, n
+        assert f(**{n: at["ws"] + 256}) == (EOVERLAP if n == "pk" else EWS), n
+    assert f(ws=at["y"]) == EWS
+    assert f(pb=need - 1) == EWS and f(nb=nb - 1) == EWS and f(ws=at["ws"] + 64) == EWS
+    for kw in (dict(eps1=float("inf")), dict(eps2=float("nan")), dict(attention=2)):
+        assert f(**kw) == EARG, kw
+    assert f(dtype=7) == EDTYPE and f(s=bshape(window=6)) == ESHAPE
+    # what only the separate layers cover
+    assert f(dtype=B.F32) == EUNSUP
+    for kw in (dict(hidden=0), dict(hidden=-4), dict(hidden=190),
+               dict(s=bshape(channels=288)),               # > 256
+               dict(s=bshape(channels=90, heads=3)),       # not a multiple of 4
+               dict(s=bshape(channels=60, heads=4))):      # d_h = 15
+        assert f(**kw) == EUNSUP, kw
+    assert f(s=bshape(batch=0), x=None, y=None, ws=None) == OK

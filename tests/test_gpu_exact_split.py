@@ -19,9 +19,11 @@ def softmax64(q, k, v):
     return torch.softmax(q.shape[-1] ** -0.5 * (q @ k.transpose(-1, -2)), -1) @ v
 
 
-# one and four query tiles per wave, several workgroups per unit, every width
-@pytest.mark.parametrize("N,d", [(64, 8), (128, 12), (192, 16), (256, 20), (256, 24), (512, 28),
-                                 (1024, 30), (256, 32)])
+# The fp32 matrix cores (N = 64, 128; one query tile per wave), the split kernel (256 to
+# 448 in steps of 64 with four to seven waves, and multiples of 512 with eight, several
+# workgroups per unit), and multiples of 64 that neither takes (192, 576); every width
+@pytest.mark.parametrize("N,d", [(64, 8), (128, 12), (192, 16), (256, 20), (256, 24), (320, 16),
+                                 (384, 8), (448, 30), (512, 28), (576, 30), (1024, 30), (256, 32)])
 @pytest.mark.parametrize("scale", [1e-3, 1.0, 4.0])
 def test_accuracy(N, d, scale):
     q, k, v = qkv(3, N, d, N + d, scale)
@@ -40,7 +42,7 @@ def test_accuracy(N, d, scale):
     assert rel <= bound
 
 
-@pytest.mark.parametrize("N", [64, 256, 512])
+@pytest.mark.parametrize("N", [64, 256, 320, 512])
 def test_values_that_are_not_finite(N):
     """-inf keys mask (probability 0), inf in V and NaN reach what they touch and
     nothing else: as a plain fp32 evaluation gives it."""

@@ -1,8 +1,8 @@
-"""Token counts that are not a multiple of 16, through the automatic choice:
-the tiled kernel with a partial last token tile, against the float64 oracle
-and the generic kernel.  Covers one to three landmark-tile counts per residue
-of N mod 32 (a missing second tile, a partial one), single tokens, m = N, both
-landmark modes and values that must not leak from the repeated rows."""
+"""Token counts that are not a multiple of 16, through the automatic choice: the tiled
+kernel with a partial last token tile, against the float64 oracle and, for its error and
+for values that are not finite, the generic kernel that ran such shapes before.  Covers
+one to four landmark-tile counts per residue of N mod 32 (a missing second tile, a
+partial one), single tokens, m = N and both landmark modes."""
 import numpy as np
 import pytest
 import torch
@@ -116,6 +116,11 @@ def test_neighbours_untouched(dtype):
         alone = B.nystra_attn_forward_ex(q[u:u + 1].contiguous(), k[u:u + 1].contiguous(),
                                          v[u:u + 1].contiguous(), 7)
         assert torch.equal(alone[0], out[u])
+    for t in (q, k, v):                 # nothing of a neighbour's rows reaches a unit
+        t[3] = float("nan")
+    again = B.nystra_attn_forward_ex(q, k, v, 7)
+    assert torch.isnan(again[3]).all()
+    assert all(torch.equal(again[u], out[u]) for u in (0, 1, 2, 4, 5, 6))
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -149,8 +154,19 @@ def test_values_that_are_not_finite(N, d, m, mode, dtype):
         assert near, f"unit {u}: {int(torch.isnan(got[u]).sum())} NaN, {int(torch.isnan(ref[u]).sum())} expected"
 
 
+def test_automatic_choice_is_the_tiled_kernel():
+    """The two kernels add in other orders, so their bits tell them apart; a head width
+    without a tiled form stays with the generic one."""
+    for d, tiled in ((16, True), (22, False)):
+        t = [to_dev(x, "f32") for x in W.iid((4, 2, 100, d), seed=11, dtype="f32")]
+        auto = B.nystra_attn_forward_ex(*t, 25)
+        generic = B.nystra_attn_forward_ex(*t, 25, opts=B.make_opts(variant=B.VARIANT_GENERIC))
+        assert torch.equal(auto, generic) != tiled
+        assert (auto - generic).abs().max() <= 1e-4
+
+
 def test_named_variants_unchanged():
-    """AUTO takes the tiled kernel; by name such shapes stay GENERIC only."""
+    """By name such shapes stay GENERIC only."""
     assert B.nystra_select_variant(100, 16, 25) == B.VARIANT_GENERIC
     q = torch.zeros((1, 1, 100, 16), device="cuda")
     with pytest.raises(B.NystraError):
