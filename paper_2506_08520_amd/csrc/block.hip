@@ -317,7 +317,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
         }
     };
     u16x2 top = {0, 0};
-    auto stash = [&]() {
+    auto stash = [&](auto clean) {
 #pragma unroll
         for (int j = 0; j < F::ap; ++j) {
             const int at = wide_slot<E>((tid + 256 * j) / F::slots, akp);
@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     x[e] = __uint_as_float(ra[j][e >> 2].w[e & 3]);
-                split3_bf16(x, As[at], As[kSlots + at], As[2 * kSlots + at], top);
+                split3_bf16<clean>(x, As[at], As[kSlots + at], As[2 * kSlots + at], top);
             }
         }
 #pragma unroll
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     x[e] = __uint_as_float(rb[e].w[j]);
-                split3_bf16(x, Bs[at], Bs[kSlots + at], Bs[2 * kSlots + at], top);
+                split3_bf16<clean>(x, Bs[at], Bs[kSlots + at], Bs[2 * kSlots + at], top);
             }
         }
     };
@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(256) block_gemm_wide_kernel(BlockArgs a)
                 acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
         fetch(0);
         for (int k0 = 0; k0 < a.C; k0 += F::BK) {
-            stash();
+            stash(f32);   // the first time as if every value were finite
             __syncthreads();
             if (k0 + F::BK < a.C)   // uniform
                 fetch(k0 + F::BK);
@@ -1167,7 +1167,6 @@ block_gemm_rw_kernel(BlockArgs a)
         }
         // operands of this tile, zero from C on
         bf8 ab[L::NP][KS];
-        u16x2 atop = {0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int k0 = 32 * s + 8 * g;
@@ -1177,18 +1176,29 @@ block_gemm_rw_kernel(BlockArgs a)
                 for (int w = 0; w < RW; ++w)
                     raw[s][w] = k0 + EW * w < a.C ? raw[s][w] : 0u;
             }
-            if constexpr (BF) {
-                const U16B u = {{raw[s][0], raw[s][1], raw[s][2], raw[s][3]}};
-                ab[0][s] = __builtin_bit_cast(bf8, u);
-            } else {
-                float f[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    f[e] = __uint_as_float(raw[s][e]);
-                split3_bf16(f, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s], atop);
-            }
         }
+        u16x2 atop = {0, 0};
+        auto take = [&](auto clean) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                if constexpr (BF) {
+                    const U16B u = {{raw[s][0], raw[s][1], raw[s][2], raw[s][3]}};
+                    ab[0][s] = __builtin_bit_cast(bf8, u);
+                } else {
+                    float f[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        f[e] = __uint_as_float(raw[s][e]);
+                    split3_bf16<clean>(f, ab[0][s], ab[L::NP / 2][s], ab[L::NP - 1][s], atop);
+                }
+            }
+        };
+        take(std::false_type{});
         const bool inf = !BF && (colsinf || __builtin_amdgcn_ballot_w64(not_finite(atop)) != 0);
+        if constexpr (!BF) {
+            if (inf)   // uniform
+                take(std::true_type{});
+        }
         if (++sub == 4) {   // uniform
             sub = 0;
             rows4(rt + stride);

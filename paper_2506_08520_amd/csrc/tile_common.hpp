@@ -133,11 +133,13 @@ __device__ inline void split_bf16(const float (&x)[8], bf8 &hi, bf8 &lo)
 // upper halves).  Its products with the other side's zero
 // terms are NaN all the same: `top` keeps the largest magnitudes (upper halves) of
 // what was split, and where not_finite(top) a tile takes the fp32 matrix instruction
-// (join3_bf16, mfma_f32x8).
+// (join3_bf16, mfma_f32x8).  CLEAN = false leaves the zeroing to the caller, who looks at
+// `top` after several splits and repeats them.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ inline bool not_finite(u16x2 top) { return top.x >= 0x7f80 || top.y >= 0x7f80; }
 
+template <bool CLEAN = true>
 __device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l, u16x2 &top)
 {
     const NegSel s = neg_selectors();
@@ -153,7 +155,7 @@ __device__ inline void split3_bf16(const float (&x)[8], bf8 &h, bf8 &m, bf8 &l, 
 #pragma unroll
     for (int e = 0; e < 8; ++e)
         r[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
-    if (__builtin_expect(not_finite(own), 0)) {
+    if (CLEAN && __builtin_expect(not_finite(own), 0)) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             if (!(fabsf(x[e]) < INFINITY))
